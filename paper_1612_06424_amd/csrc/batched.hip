@@ -22,6 +22,7 @@
 
 #include "dd_dslash.h"
 #include "dd_eo.h"
+#include "dd_eo_tile.h"
 
 namespace dd {
 
@@ -80,6 +81,8 @@ struct BEODom {
     int ntile;         // tiles of kBeoNT pairs per slice
     int tc;            // slices per chunk
     int blocked;       // brick tiles (pair_site)
+    EoTile ts;         // LDS-tile form: its bricks (nblk of them)
+    int cpw;           // and columns per workgroup
 };
 static_assert(sizeof(BEODom) % 8 == 0, "descriptor layout must be the same on host and device");
 
@@ -126,6 +129,66 @@ __global__ __launch_bounds__(kBeoNT) void k_beo_hop(const BEODom* __restrict__ d
                                                       in + off, self != nullptr ? self + off : nullptr, out + off,
                                                       aux != nullptr ? aux + off : nullptr, live, blk % d.ntile,
                                                       blk / d.ntile, d.tc, d.blocked, slot, (size_t)d.nblk);
+}
+
+// The same launch in the LDS-tile form (dd_eo_tile.h): a workgroup loops over up to cpw columns of a
+// brick of its domain.  f = +1 for D^+, -1 for D.
+template <typename R, int EPI, bool SCHUR, bool REC>
+__global__ __launch_bounds__(kTileNT, 2) void k_beo_lds(const BEODom* __restrict__ doms, int ndom,
+                                                       const cpx<R>* __restrict__ in, const cpx<R>* __restrict__ self,
+                                                       cpx<R>* __restrict__ out, const cpx<R>* __restrict__ aux, R f,
+                                                       int remap, double* __restrict__ partial,
+                                                       const ColState* __restrict__ st) {
+    const int bid = remap ? xcd_remap(blockIdx.x, gridDim.x) : (int)blockIdx.x;
+    int lo = 0, hi = ndom - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (doms[mid].blk0 <= bid) lo = mid;
+        else hi = mid - 1;
+    }
+    const BEODom& d = doms[lo];
+    const int lb = bid - d.blk0, grp = lb / d.nblk;
+    const Geo g = d.g;
+    const EoTile ts = d.ts;
+    EoTileArgs<R> a;
+    a.U = (const cpx<R>*)(REC ? d.Ueo12 : d.Ueo);
+    a.in = in + d.hoff;
+    a.self = SCHUR ? self + d.hoff : nullptr;
+    a.out = out + d.hoff;
+    a.aux = aux != nullptr ? aux + d.hoff : nullptr;
+    a.a_self = SCHUR ? R(d.mass) : R(0);
+    a.c_hop = SCHUR ? R(-0.25 / d.mass) : R(1);
+    a.f = f;
+    a.p_out = SCHUR ? 0 : 1;
+    a.st = st != nullptr ? st + d.seg0 : nullptr;
+    a.partial = partial + (size_t)d.slot0 * 3;
+    a.nblk = d.nblk;
+    eo_tile_body<R, EPI, SCHUR, REC, !SCHUR>(g, ts, a, lb - grp * d.nblk, grp * d.cpw,
+                                             min(d.ncol, grp * d.cpw + d.cpw));
+}
+
+template <typename R, bool REC>
+void launch_beo_lds(hipStream_t s, int dag, int epi, bool schur, unsigned nblk, const BEODom* doms, int ndom,
+                    const cpx<R>* in, const cpx<R>* self, cpx<R>* out, const cpx<R>* aux, int remap, double* partial,
+                    const ColState* st) {
+    const dim3 grid(nblk), block(kTileNT);
+    const R f = R(dag ? 1 : -1);
+    if (!schur) {
+        hipLaunchKernelGGL((k_beo_lds<R, EPI_STORE, false, REC>), grid, block, 0, s, doms, ndom, in, self, out, aux, f,
+                           remap, partial, st);
+        return;
+    }
+#define DD_BLDS_CASE(E)                                                                                              \
+    hipLaunchKernelGGL((k_beo_lds<R, E, true, REC>), grid, block, 0, s, doms, ndom, in, self, out, aux, f, remap, \
+                       partial, st)
+    switch (epi) {
+        case EPI_STORE: DD_BLDS_CASE(EPI_STORE); break;
+        case EPI_DOT_AUX: DD_BLDS_CASE(EPI_DOT_AUX); break;
+        case EPI_TS: DD_BLDS_CASE(EPI_TS); break;
+        case EPI_RESID: DD_BLDS_CASE(EPI_RESID); break;
+        default: DD_BLDS_CASE(EPI_NORM); break;
+    }
+#undef DD_BLDS_CASE
 }
 
 template <typename R, int DAG, bool SCHUR, int KC, bool REC>
@@ -307,6 +370,7 @@ struct BatchEOSystem : System {
     unsigned nblk64 = 0, nblk32 = 0;   // workgroups of a launch per precision
     int remap[2] = {0, 0};             // XCD-contiguous workgroup ranges per precision
     int kc[2] = {1, 1};                // columns per workgroup per precision
+    bool lds[2] = {false, false};      // LDS-tile form per precision
     bool rec32 = false;                // FP32 descriptors carry two-row links
     cpx<double>* tmp64 = nullptr;
     cpx<float>* tmp32 = nullptr;
@@ -317,12 +381,27 @@ struct BatchEOSystem : System {
         const unsigned nblk = this->nblk != 0 ? this->nblk : (sizeof(R) == 8 ? nblk64 : nblk32);
         const int rm = remap[sizeof(R) == 8 ? 0 : 1];
         const int k = kc[sizeof(R) == 8 ? 0 : 1];
-        const bool rec = sizeof(R) == 4 && rec32 && k > 1;
+        const bool tile = lds[sizeof(R) == 8 ? 0 : 1];
+        const bool rec = sizeof(R) == 4 && rec32 && (tile || k > 1);
         for (int half = 0; half < 2; half++) {
             const int e = half ? epi : EPI_STORE;
             hipEvent_t ev = nullptr;
             if (c->timing) timing_begin(c, &ev);
-            if (half == 0) {
+            if (tile) {
+                const cpx<R>* src = half ? (const cpx<R>*)tmp : in;
+                cpx<R>* dst = half ? out : tmp;
+                bool done = false;
+                if constexpr (sizeof(R) == 4) {
+                    if (rec) {
+                        launch_beo_lds<R, true>(c->stream, dag, e, half != 0, nblk, dv, ndom, src, in, dst, aux, rm,
+                                                partial, st);
+                        done = true;
+                    }
+                }
+                if (!done)
+                    launch_beo_lds<R, false>(c->stream, dag, e, half != 0, nblk, dv, ndom, src, in, dst, aux, rm,
+                                             partial, st);
+            } else if (half == 0) {
                 if (dag)
                     launch_beo<R, 1, false>(c->stream, k, rec, e, nblk, dv, ndom, in, nullptr, tmp, nullptr, rm,
                                             partial, st);
@@ -343,10 +422,12 @@ struct BatchEOSystem : System {
                 }
                 const double extra = (half ? 24.0 : 0.0) + (e == EPI_DOT_AUX || e == EPI_RESID ? 24.0 : 0.0);
                 const double bytes = ((48.0 + extra) * sc * c->bill_frac + (rec ? 96.0 : 144.0) * s) * sizeof(R);
-                const std::string name = std::string("k_beo_hop<") + (sizeof(R) == 8 ? "double" : "float") + ", " +
-                                         std::to_string(dag ? 1 : 0) + ", " + std::to_string(e) + ", " +
-                                         (half ? "true, " : "false, ") + std::to_string(k) +
-                                         (rec ? ", true>" : ", false>");
+                const std::string real = sizeof(R) == 8 ? "double, " : "float, ";
+                const std::string name =
+                    tile ? "k_beo_lds<" + real + std::to_string(e) + (half ? ", true, " : ", false, ") +
+                               (rec ? "true>" : "false>")
+                         : "k_beo_hop<" + real + std::to_string(dag ? 1 : 0) + ", " + std::to_string(e) + ", " +
+                               (half ? "true, " : "false, ") + std::to_string(k) + (rec ? ", true>" : ", false>");
                 timing_end(c, ev, name, bytes);
             }
         }
@@ -543,12 +624,14 @@ dd_status solve_batch_eo(dd_ctx* c, const std::vector<Item>& its, const dd_solve
             d.blk0 = blk;
             d.ntile = ((it.g.L3 >> 1) + kBeoNT - 1) / kBeoNT;
             d.tc = std::min(tc, it.g.nt);
-            d.nblk = d.ntile * ((it.g.nt + d.tc - 1) / d.tc);
-            d.blocked = blocked && it.g.L % 4 == 0;
+            d.blocked = (blocked & 1) && it.g.L % 4 == 0;
+            d.ts = eo_tile_shape(it.g.L, it.g.nt);
+            d.cpw = std::min(kc, it.ncol);
+            d.nblk = (blocked & 8) ? eo_tile_blocks(d.ts) : d.ntile * ((it.g.nt + d.tc - 1) / d.tc);
             d.slot0 = slot;
             h->push_back(d);
             for (int j = 0; j < it.ncol; j++) sp0->push_back(slot + j * d.nblk);
-            blk += d.nblk * it.ncol / kc;
+            blk += (blocked & 8) ? d.nblk * ((it.ncol + d.cpw - 1) / d.cpw) : d.nblk * it.ncol / kc;
             slot += d.nblk * it.ncol;
             seg += it.ncol;
         }
@@ -585,7 +668,8 @@ dd_status solve_batch_eo(dd_ctx* c, const std::vector<Item>& its, const dd_solve
             return true;
         };
         const auto hit = c->sched.find(key);
-        if (hit != c->sched.end() && kc_ok(hit->second.kc)) {
+        if (hit != c->sched.end() &&
+            ((hit->second.blocked & 8) ? hit->second.kc >= 1 : kc_ok(hit->second.kc))) {
             tc = hit->second.tc;
             rmap = hit->second.remap;
             kcb = hit->second.kc;
@@ -605,38 +689,43 @@ dd_status solve_batch_eo(dd_ctx* c, const std::vector<Item>& its, const dd_solve
             };
             bool any4 = false;  // some domain can take brick tiles
             for (const Item& it : its) any4 = any4 || it.g.L % 4 == 0;
-            for (int t : {1, 2, 4, 8}) {
-                for (int kc : {1, 2}) {
-                    for (int bl = 0; bl < (any4 ? 2 : 1); bl++) {
-                        if (!kc_ok(kc)) continue;
-                        S.kc[kind] = kc;
-                        S.nblk = (unsigned)build(t, kc, bl, kind, &hk, &sp);
-                        S.host = hk;
-                        e = upload(kind, hk);
-                        if (e != DD_OK) break;
-                        for (int rm = 0; rm < 2; rm++) {
-                            S.remap[kind] = rm;
-                            run();
-                            run();
-                            (void)hipEventRecord(ea, c->stream);
-                            for (int r = 0; r < 3; r++) run();
-                            (void)hipEventRecord(eb, c->stream);
-                            (void)hipEventSynchronize(eb);
-                            float ms = 0;
-                            (void)hipEventElapsedTime(&ms, ea, eb);
-                            if (ms < best) {
-                                best = ms;
-                                tc = t;
-                                rmap = rm;
-                                kcb = kc;
-                                blk = bl;
-                            }
+            // the best of two timings of three applications
+            auto try_shape = [&](int t, int kc, int bl, int rm0) -> dd_status {
+                S.kc[kind] = kc;
+                S.lds[kind] = (bl & 8) != 0;
+                S.nblk = (unsigned)build(t, kc, bl, kind, &hk, &sp);
+                S.host = hk;
+                const dd_status ee = upload(kind, hk);
+                if (ee != DD_OK) return ee;
+                for (int rm = rm0; rm < 2; rm++) {
+                    S.remap[kind] = rm;
+                    run();
+                    run();
+                    for (int rep = 0; rep < 2; rep++) {
+                        (void)hipEventRecord(ea, c->stream);
+                        for (int r = 0; r < 3; r++) run();
+                        (void)hipEventRecord(eb, c->stream);
+                        (void)hipEventSynchronize(eb);
+                        float ms = 0;
+                        (void)hipEventElapsedTime(&ms, ea, eb);
+                        if (ms < best) {
+                            best = ms;
+                            tc = t;
+                            rmap = rm;
+                            kcb = kc;
+                            blk = bl;
                         }
                     }
-                    if (e != DD_OK) break;
                 }
-                if (e != DD_OK) break;
-            }
+                return DD_OK;
+            };
+            for (int t : {1, 2, 4, 8})
+                for (int kc : {1, 2})
+                    for (int bl = 0; bl < (any4 ? 2 : 1); bl++)
+                        if (e == DD_OK && kc_ok(kc)) e = try_shape(t, kc, bl, 0);
+            // the LDS-tile form, the columns of a domain in 1 to 3 groups
+            for (int kc : {12, 6, 4})
+                if (e == DD_OK) e = try_shape(1, kc, 8, 1);
             c->timing = saved;
             S.nblk = 0;  // launches size themselves from nblk64 / nblk32 again
             (void)hipEventDestroy(ea);
@@ -652,6 +741,7 @@ dd_status solve_batch_eo(dd_ctx* c, const std::vector<Item>& its, const dd_solve
         }
         S.remap[kind] = rmap;
         S.kc[kind] = kcb;
+        S.lds[kind] = (blk & 8) != 0;
         const unsigned nb = (unsigned)build(tc, kcb, blk, kind, &hk, &lay.sp0[kind]);
         if (kind == 0) {
             S.nblk64 = nb;

@@ -15,7 +15,7 @@
 #include <vector>
 
 #include "dd_eo.h"
-#include "dd_eo_lds.h"
+#include "dd_eo_tile.h"
 
 namespace dd {
 
@@ -86,16 +86,12 @@ __global__ __launch_bounds__(NT, eo_waves<R>()) void k_eo_hop_nt(Geo g, const cp
                                                       remap, blocked, partial, st);
 }
 
-// The LDS-tile form of the half hop (dd_eo_lds.h): one slice of a brick of rows per
-// workgroup, cpw columns per workgroup, links of two rows each (SU(3)).
-template <typename R, int DAG, int EPI, bool SELF, int LH, bool NTS>
-__global__ __launch_bounds__(kLdsNT, 1) void k_eo_lds(Geo g, const cpx<R>* __restrict__ U12, R a_self, R c_hop,
-                                                     int p_out, const cpx<R>* __restrict__ in,
-                                                     const cpx<R>* __restrict__ self, cpx<R>* __restrict__ out,
-                                                     const cpx<R>* __restrict__ aux, int ncol, int cpw, int remap,
-                                                     double* __restrict__ partial, const ColState* __restrict__ st) {
-    eo_lds_body<R, DAG, EPI, SELF, LH, NTS>(g, U12, a_self, c_hop, p_out, in, self, out, aux, ncol, cpw, remap,
-                                            partial, st);
+// The LDS-tile form of the half hop (dd_eo_tile.h): workgroup -> brick, then group of cpw columns.
+template <typename R, int EPI, bool SELF, bool REC, bool NTS>
+__global__ __launch_bounds__(kTileNT, 2) void k_eo_lds(Geo g, EoTile ts, EoTileArgs<R> a, int ncol, int cpw, int remap) {
+    const int lb = remap ? xcd_remap(blockIdx.x, gridDim.x) : (int)blockIdx.x;
+    const int grp = lb / a.nblk;
+    eo_tile_body<R, EPI, SELF, REC, NTS>(g, ts, a, lb - grp * a.nblk, grp * cpw, min(ncol, grp * cpw + cpw));
 }
 
 // full field [ncol][12][nsite] <-> even / odd half fields [ncol][12][nsite / 2]
@@ -188,6 +184,36 @@ constexpr int kEoNT = 256;
 // workgroups per column: tiles of kEoNT pairs per slice x chunks of tc slices
 int eo_blocks(const Geo& g, int tc) { return (((g.L3 >> 1) + kEoNT - 1) / kEoNT) * ((g.nt + tc - 1) / tc); }
 
+// The LDS-tile form with the columns in `parts` groups.
+StencilSched eo_tile_sched(int ncol, int parts) {
+    StencilSched sc;
+    sc.nt = kEoNT;
+    sc.tc = 1;
+    sc.remap = 1;
+    sc.kc = (ncol + parts - 1) / parts;
+    sc.blocked = 8;
+    return sc;
+}
+
+// The shape of a launch that is not tuned.  The LDS-tile form needs a workgroup per CU with columns
+// to loop over (FP64, 12 columns: 16 x 32^3, 1024 bricks, 418 us against the sweep's 579; 32 x 16^3, 256
+// bricks, 86 against 140; 8 x 16^3, 64 bricks, 36 against 31).  Below that the sweep of one slice per chunk,
+// one column per thread: the most workgroups and the shortest serial chain (one column on
+// 32 x 16^3, chunks of 1 and 4 slices: FP32 10.5 and 25 us, FP64 17.7 and 36).
+StencilSched eo_default_sched(const Geo& g, int ncol) {
+    if (ncol >= 4 && eo_tile_blocks(eo_tile_shape(g.L, g.nt)) >= 256) return eo_tile_sched(ncol, 1);
+    StencilSched sc;
+    sc.nt = kEoNT;
+    sc.tc = 1;
+    return sc;
+}
+
+// partial slots per column of a launch with shape sc
+int eo_slots(const Geo& g, const StencilSched& sc) {
+    if (!(sc.blocked & 8)) return eo_blocks(g, sc.tc);
+    return eo_tile_blocks(eo_tile_shape(g.L, g.nt));
+}
+
 template <typename R, int DAG, bool SELF, int KC, bool REC, bool NTS>
 void launch_eo_epi(hipStream_t s, int epi, dim3 grid, const Geo& g, const cpx<R>* U, R a_self, R c_hop, int p_out,
                    const cpx<R>* in, const cpx<R>* self, cpx<R>* out, const cpx<R>* aux, int ncol, int tc,
@@ -243,34 +269,26 @@ void launch_eo_kc(hipStream_t s, int kc, bool rec, bool nts, int epi, dim3 grid,
 #undef DD_EO_KC
 }
 
-// The LDS-tile form applies to FP32 fields with L = 32 or 16 whose links are SU(3)
-// (two rows each).
-template <typename R>
-bool eo_lds_ok(const Geo& g, const void* U12) {
-    return sizeof(R) == 4 && U12 != nullptr && (g.L == 32 || g.L == 16);
-}
-
-template <typename R, int D, bool SF, int LH>
-void launch_eo_lds_lh(hipStream_t s, int epi, bool nts, dim3 grid, const Geo& g, const cpx<R>* U12, R a_self,
-                      R c_hop, int p_out, const cpx<R>* in, const cpx<R>* self, cpx<R>* out, const cpx<R>* aux,
-                      int ncol, int cpw, int remap, double* partial, const ColState* st) {
-    const dim3 block(kLdsNT);
-#define DD_LDS_CASE(E)                                                                                              \
-    if (nts)                                                                                                        \
-        hipLaunchKernelGGL((k_eo_lds<R, D, E, SF, LH, true>), grid, block, 0, s, g, U12, a_self, c_hop, p_out, in, \
-                           self, out, aux, ncol, cpw, remap, partial, st);                                          \
-    else                                                                                                            \
-        hipLaunchKernelGGL((k_eo_lds<R, D, E, SF, LH, false>), grid, block, 0, s, g, U12, a_self, c_hop, p_out, in, \
-                           self, out, aux, ncol, cpw, remap, partial, st)
-    if constexpr (!SF) {
-        DD_LDS_CASE(EPI_STORE);  // the first half of the Schur operator
-    } else {
-        switch (epi) {
-            case EPI_STORE: DD_LDS_CASE(EPI_STORE); break;
-            case EPI_DOT_AUX: DD_LDS_CASE(EPI_DOT_AUX); break;
-            case EPI_TS: DD_LDS_CASE(EPI_TS); break;
-            default: DD_LDS_CASE(EPI_NORM); break;
-        }
+// One launch of the LDS-tile form.  The first half hop's output (no self field) is stored
+// non-temporally: it would push the input halos out of L2 (FP64 on 32 x 16^3, 12 columns: 85 us
+// against 102); the second half's, which the vector kernels read next, is not (FP32 there 50 us
+// against 56).
+template <typename R, bool REC>
+void launch_eo_lds(hipStream_t s, int epi, bool sf, const Geo& g, const EoTile& ts, const EoTileArgs<R>& a, int ncol,
+                   int cpw, int remap) {
+    const dim3 grid((unsigned)(a.nblk * ((ncol + cpw - 1) / cpw))), block(kTileNT);
+    if (!sf) {
+        hipLaunchKernelGGL((k_eo_lds<R, EPI_STORE, false, REC, true>), grid, block, 0, s, g, ts, a, ncol, cpw, remap);
+        return;
+    }
+#define DD_LDS_CASE(E) \
+    hipLaunchKernelGGL((k_eo_lds<R, E, true, REC, false>), grid, block, 0, s, g, ts, a, ncol, cpw, remap)
+    switch (epi) {
+        case EPI_STORE: DD_LDS_CASE(EPI_STORE); break;
+        case EPI_DOT_AUX: DD_LDS_CASE(EPI_DOT_AUX); break;
+        case EPI_TS: DD_LDS_CASE(EPI_TS); break;
+        case EPI_RESID: DD_LDS_CASE(EPI_RESID); break;
+        default: DD_LDS_CASE(EPI_NORM); break;
     }
 #undef DD_LDS_CASE
 }
@@ -283,51 +301,48 @@ void launch_eo_lds_lh(hipStream_t s, int epi, bool nts, dim3 grid, const Geo& g,
 // U: the checkerboard links; U12 (nullable): the same links as two rows each,
 // which launches with kc > 1 read instead.
 //
-// Tile flag bit 3 selects the LDS-tile form (eo_lds_ok; one slice per workgroup, so
-// its partial slots are those of tc = 1) with kc columns per workgroup and bit 2
-// for non-temporal stores; where it does not apply the time sweep runs instead.
+// Tile flag bit 3 selects the LDS-tile form with kc columns per workgroup (its partial slots:
+// eo_slots); of its launches only those with a self field form sums.
 template <typename R>
 void launch_eo_hop(dd_ctx* c, const Geo& g, const cpx<R>* U, const cpx<R>* U12, double a_self, double c_hop,
                    int p_out, int dag, int epi, const cpx<R>* in, const cpx<R>* self, cpx<R>* out, const cpx<R>* aux,
                    int ncol, int tc, int kc, int remap, int blocked, double* partial, const ColState* st) {
     const bool sf = self != nullptr && a_self != 0;
-    if constexpr (sizeof(R) == 4)
-    if ((blocked & 8) && eo_lds_ok<R>(g, U12) && !(epi == EPI_RESID) && (sf || epi == EPI_STORE)) {
+    if (blocked & 8) {
         const int cpw = std::max(1, std::min(kc, ncol));
-        const bool nts = (blocked & 4) != 0;
-        const int ntile = ((g.L3 >> 1) + kLdsNT - 1) / kLdsNT;
-        const dim3 grid((unsigned)(ntile * g.nt * ((ncol + cpw - 1) / cpw)));
+        const bool rec = U12 != nullptr;
+        const EoTile ts = eo_tile_shape(g.L, g.nt);
+        EoTileArgs<R> a;
+        a.U = rec ? U12 : U;
+        a.in = in;
+        a.self = self;
+        a.out = out;
+        a.aux = aux;
+        a.a_self = R(a_self);
+        a.c_hop = R(c_hop);
+        a.f = R(dag ? 1 : -1);
+        a.p_out = p_out;
+        a.st = st;
+        a.partial = partial;
+        a.nblk = eo_tile_blocks(ts);
         hipEvent_t ev = nullptr;
         if (c->timing) timing_begin(c, &ev);
-#define DD_LDS_LAUNCH(D, SF, LH)                                                                                    \
-    launch_eo_lds_lh<R, D, SF, LH>(c->stream, epi, nts, grid, g, U12, R(a_self), R(c_hop), p_out, in, self, out, aux, \
-                                   ncol, cpw, remap, partial, st)
-#define DD_LDS_LH(D, SF)                 \
-    if (g.L == 32) DD_LDS_LAUNCH(D, SF, 16); \
-    else DD_LDS_LAUNCH(D, SF, 8)
-        if (dag) {
-            if (sf) DD_LDS_LH(1, true);
-            else DD_LDS_LH(1, false);
+        if constexpr (sizeof(R) == 4) {
+            if (rec) launch_eo_lds<R, true>(c->stream, epi, sf, g, ts, a, ncol, cpw, remap);
+            else launch_eo_lds<R, false>(c->stream, epi, sf, g, ts, a, ncol, cpw, remap);
         } else {
-            if (sf) DD_LDS_LH(0, true);
-            else DD_LDS_LH(0, false);
+            launch_eo_lds<R, false>(c->stream, epi, sf, g, ts, a, ncol, cpw, remap);
         }
-#undef DD_LDS_LH
-#undef DD_LDS_LAUNCH
         if (c->timing) {
             const double nh = (double)(g.nsite >> 1);
-            const double extra = (sf || epi == EPI_TS ? 24.0 : 0.0) + (epi == EPI_DOT_AUX ? 24.0 : 0.0);
-            const double bytes = nh * ((48.0 + extra) * ncol * c->bill_frac + 96.0) * sizeof(R);
-            const std::string name = std::string("k_eo_lds<float, ") + std::to_string(dag ? 1 : 0) + ", " +
+            const double extra = (sf ? 24.0 : 0.0) + (epi == EPI_DOT_AUX || epi == EPI_RESID ? 24.0 : 0.0);
+            const double bytes = nh * ((48.0 + extra) * ncol * c->bill_frac + (rec ? 96.0 : 144.0)) * sizeof(R);
+            const std::string name = std::string("k_eo_lds<") + (sizeof(R) == 8 ? "double" : "float") + ", " +
                                      std::to_string(epi) + (sf ? ", true, " : ", false, ") +
-                                     std::to_string(g.L / 2) + (nts ? ", true>" : ", false>");
+                                     (rec ? "true, " : "false, ") + (sf ? "false>" : "true>");
             timing_end(c, ev, name, bytes);
         }
         return;
-    }
-    if (blocked & 8) {  // the LDS form does not apply here: the time sweep of one slice per chunk
-        blocked = 0;
-        kc = 1;
     }
     if (!eo_kc_ok<R>(kc, ncol)) kc = 1;
     if (g.L % 4 != 0) blocked &= ~1;
@@ -402,9 +417,9 @@ struct EOSystem : System {
 // operator of this geometry and column count at first use (chunks of 1, 2,
 // 4, 8 slices, workgroups in hardware order or XCD-contiguous ranges, 1 or 2
 // columns per thread where allowed, row or brick tiles, tiles or chunks
-// adjacent, plain or non-temporal output stores with two columns), cached in the
-// context like the stencil shapes; small fields take 4 slices, no remap, one
-// column, row tiles, untimed.
+// adjacent, plain or non-temporal output stores with two columns; the LDS-tile form with the
+// columns in 1 to 3 groups), cached in the context like the stencil shapes; small fields take
+// eo_default_sched, untimed.
 template <typename R>
 StencilSched eo_tune(dd_ctx* c, EOSystem& S, const cpx<R>* UR, const cpx<R>* UR12, cpx<R>* tmp, const cpx<R>* in,
                      cpx<R>* out) {
@@ -414,10 +429,7 @@ StencilSched eo_tune(dd_ctx* c, EOSystem& S, const cpx<R>* UR, const cpx<R>* UR1
                             std::to_string(g.whole);
     const auto hit = c->sched.find(key);
     if (hit != c->sched.end()) return hit->second;
-    StencilSched best;
-    best.nt = kEoNT;
-    best.tc = std::min(4, g.nt);
-    best.kc = 1;
+    StencilSched best = eo_default_sched(g, S.ncol);
     if ((size_t)g.nsite * S.ncol >= ((size_t)1 << 18)) {
         hipEvent_t a, b;
         if (hipEventCreate(&a) == hipSuccess && hipEventCreate(&b) == hipSuccess) {
@@ -448,7 +460,8 @@ StencilSched eo_tune(dd_ctx* c, EOSystem& S, const cpx<R>* UR, const cpx<R>* UR1
                             if (t > g.nt || !eo_kc_ok<R>(kc, S.ncol) || ((bl & 1) && g.L % 4 != 0)) continue;
                             if ((bl & 4) && kc == 1) continue;  // non-temporal stores: kc > 1 only
                             if ((bl & 2) && (g.nt + t - 1) / t < 2) continue;  // one chunk: the same order
-                            StencilSched sc = best;
+                            StencilSched sc;
+                            sc.nt = kEoNT;
                             sc.tc = t;
                             sc.remap = rm;
                             sc.kc = kc;
@@ -459,23 +472,16 @@ StencilSched eo_tune(dd_ctx* c, EOSystem& S, const cpx<R>* UR, const cpx<R>* UR1
                                 best = sc;
                             }
                         }
-            // the LDS-tile form: columns per workgroup, XCD remap, store form
-            if (eo_lds_ok<R>(g, UR12))
-                for (int cpw : {12, 6, 4, 3, 2, 1})
-                    for (int rm = 0; rm < 2; rm++)
-                        for (int nts = 0; nts < 2; nts++) {
-                            if (cpw > S.ncol) continue;
-                            StencilSched sc = best;
-                            sc.tc = 1;
-                            sc.remap = rm;
-                            sc.kc = cpw;
-                            sc.blocked = 8 | (nts ? 4 : 0);
-                            const float ms = time_shape(sc);
-                            if (ms < best_ms) {
-                                best_ms = ms;
-                                best = sc;
-                            }
-                        }
+            // the LDS-tile form: columns per workgroup
+            for (int parts : {1, 2, 3}) {
+                if (parts > S.ncol) continue;
+                StencilSched sc = eo_tile_sched(S.ncol, parts);
+                const float ms = time_shape(sc);
+                if (ms < best_ms) {
+                    best_ms = ms;
+                    best = sc;
+                }
+            }
             c->timing = saved;
             (void)hipEventDestroy(a);
             (void)hipEventDestroy(b);
@@ -528,8 +534,9 @@ void launch_eo_merge(dd_ctx* c, const Geo& g, int ncol, const cpx<double>* ev, c
 }
 void launch_eo_hop64(dd_ctx* c, const Geo& g, const cpx<double>* Ueo, double a_self, double c_hop, int p_out, int dag,
                      const cpx<double>* in, const cpx<double>* self, cpx<double>* out, int ncol) {
-    launch_eo_hop<double>(c, g, Ueo, nullptr, a_self, c_hop, p_out, dag, EPI_STORE, in, self, out, nullptr, ncol,
-                          std::min(4, g.nt), 1, 0, 0, nullptr, nullptr);
+    const StencilSched sc = eo_default_sched(g, ncol);
+    launch_eo_hop<double>(c, g, Ueo, nullptr, a_self, c_hop, p_out, dag, EPI_STORE, in, self, out, nullptr, ncol, sc.tc,
+                          sc.kc, sc.remap, sc.blocked, nullptr, nullptr);
 }
 
 dd_status solve_eo(dd_ctx* c, const cpx<double>* U, double kappa, const Geo& g, int ncol, const cpx<double>* b,
@@ -595,14 +602,12 @@ dd_status solve_eo(dd_ctx* c, const cpx<double>* U, double kappa, const Geo& g, 
         lay.len.push_back(n);
     }
     for (int kind = 0; kind < 2; kind++) {
-        const int nblk = eo_blocks(g, S.sh[kind].tc);
+        const int nblk = eo_slots(g, S.sh[kind]);
         lay.sp0[kind].resize(ncol + 1);
         for (int k = 0; k <= ncol; k++) lay.sp0[kind][k] = k * nblk;
     }
     e = lay.upload(c, W_SEGS, &S);
     if (e != DD_OK) return e;
-    // the partial slots of the source preparation and reconstruction (chunks of min(4, nt))
-    S.nslots = std::max(S.nslots, (size_t)ncol * eo_blocks(g, std::min(4, g.nt)));
 
     // |b|^2 per column: the reference of every relative residual
     std::vector<double> bnorm;

@@ -32,7 +32,7 @@ import sys
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 # the sources that decide what the stencil kernels do and how they are launched
-STENCIL_SOURCES = ["csrc/dd_dslash.h", "csrc/dd_eo.h", "csrc/dd_eo_lds.h", "csrc/dd_wilson.h", "csrc/dd_internal.h",
+STENCIL_SOURCES = ["csrc/dd_dslash.h", "csrc/dd_eo.h", "csrc/dd_eo_tile.h", "csrc/dd_wilson.h", "csrc/dd_internal.h",
                    "csrc/dirac.hip", "csrc/evenodd.hip", "csrc/batched.hip", "csrc/tune.hip", "tune_cache_mi355x.txt"]
 
 
@@ -90,9 +90,9 @@ column count when it is 1) (epilogue 0 store, 1 <aux, D in>, 2 <D in, in> and |D
 4 |D in|^2, 5 kappa D_hop in); `k_eo_hop<real, dagger, epilogue, workgroup size, self, columns per
 thread, two-row links>` is the even-odd half hop (`k_eo_hop_nt` the same with non-temporal output
 stores; self = true: the second half of the Schur operator, or the source preparation /
-reconstruction), `k_eo_lds<float, dagger, epilogue, self, L/2, non-temporal>` its LDS-tile form
-(one slice per workgroup), `k_beo_hop<real, dagger, epilogue, self, columns per thread, two-row
-links>` its multi-domain form in the batched solve.  The batched solve replays its inner
+reconstruction), `k_eo_lds<real, epilogue, self, two-row links, non-temporal>` its LDS-tile form,
+`k_beo_hop<real, dagger, epilogue, self, columns per thread, two-row links>` and `k_beo_lds<real,
+epilogue, self, two-row links>` the multi-domain forms in the batched solve.  The batched solve replays its inner
 iterations as a HIP graph, whose launches the library's HIP-event timing does not see: for
 `k_beo_hop` the HIP-event column averages the eager launches only, the rocprof column all of
 them.  Algorithmic bytes per launch: V ((48 + e) ncol + 72) sizeof(real) for the full stencil,
