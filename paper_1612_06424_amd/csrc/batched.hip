@@ -163,7 +163,7 @@ __global__ __launch_bounds__(kTileNT, 2) void k_beo_lds(const BEODom* __restrict
     a.st = st != nullptr ? st + d.seg0 : nullptr;
     a.partial = partial + (size_t)d.slot0 * 3;
     a.nblk = d.nblk;
-    eo_tile_body<R, EPI, SCHUR, REC, !SCHUR>(g, ts, a, lb - grp * d.nblk, grp * d.cpw,
+    eo_tile_body<R, EPI, SCHUR, REC, !SCHUR && sizeof(R) == 8>(g, ts, a, lb - grp * d.nblk, grp * d.cpw,
                                              min(d.ncol, grp * d.cpw + d.cpw));
 }
 

@@ -219,13 +219,19 @@ __device__ __forceinline__ void eo_tile_body(const Geo& g, const EoTile& ts, con
 
     const int L = g.L, L2 = g.L2, L3 = g.L3, LH = L >> 1, nt = g.nt, nh = g.nsite >> 1;
     const uint32_t cs = (uint32_t)nh * CB, fs = 12u * cs, ls = 2u * (uint32_t)nh * CB;
-    // workgroup -> brick: time fastest within a time block, then y, z
+    // workgroup -> brick: time fastest within a time block, then groups of 4 x 2 bricks in (y, z), whose
+    // halos lie mostly inside the group (both FP64 halves on 16 x 32^3: 951 us row by row, 922 so;
+    // FP32 the same either way)
     const int ntile = ts.nty * ts.ntz;
     const int tbk = blk_lin / (ts.tb * ntile);
     const int inb = blk_lin - tbk * ts.tb * ntile;
     const int tbs = min(ts.tb, ts.ntt - tbk * ts.tb);
-    const int tile = inb / tbs;
+    int tile = inb / tbs;
     const int bt = tbk * ts.tb + (inb - tile * tbs);
+    if (ts.nty % 4 == 0 && ts.ntz % 2 == 0) {
+        const int grp = tile >> 3, in8 = tile & 7, ng = ts.nty >> 2;
+        tile = ((grp / ng) * 2 + (in8 >> 2)) * ts.nty + (grp % ng) * 4 + (in8 & 3);
+    }
     const int t0 = bt * ts.rt, y0 = (tile % ts.nty) * ts.ry, z0 = (tile / ts.nty) * ts.rz;
     const int RT = min(ts.rt, nt - t0), RY = min(ts.ry, L - y0), RZ = min(ts.rz, L - z0);
     const int blk = bt * ntile + tile;

@@ -269,16 +269,16 @@ void launch_eo_kc(hipStream_t s, int kc, bool rec, bool nts, int epi, dim3 grid,
 #undef DD_EO_KC
 }
 
-// One launch of the LDS-tile form.  The first half hop's output (no self field) is stored
-// non-temporally: it would push the input halos out of L2 (FP64 on 32 x 16^3, 12 columns: 85 us
-// against 102); the second half's, which the vector kernels read next, is not (FP32 there 50 us
-// against 56).
+// One launch of the LDS-tile form.  The FP64 first half hop's output (no self field) is stored
+// non-temporally: it would push the input halos out of L2 (both halves on 32 x 16^3, 12 columns, one after
+// the other: 223 us against 232).  In FP32 the second half finds part of a plain store's data in
+// the Infinity Cache (both halves there 94 us against 100, on 16 x 32^3 420 against 447).
 template <typename R, bool REC>
 void launch_eo_lds(hipStream_t s, int epi, bool sf, const Geo& g, const EoTile& ts, const EoTileArgs<R>& a, int ncol,
                    int cpw, int remap) {
     const dim3 grid((unsigned)(a.nblk * ((ncol + cpw - 1) / cpw))), block(kTileNT);
     if (!sf) {
-        hipLaunchKernelGGL((k_eo_lds<R, EPI_STORE, false, REC, true>), grid, block, 0, s, g, ts, a, ncol, cpw, remap);
+        hipLaunchKernelGGL((k_eo_lds<R, EPI_STORE, false, REC, sizeof(R) == 8>), grid, block, 0, s, g, ts, a, ncol, cpw, remap);
         return;
     }
 #define DD_LDS_CASE(E) \
@@ -339,7 +339,7 @@ void launch_eo_hop(dd_ctx* c, const Geo& g, const cpx<R>* U, const cpx<R>* U12, 
             const double bytes = nh * ((48.0 + extra) * ncol * c->bill_frac + (rec ? 96.0 : 144.0)) * sizeof(R);
             const std::string name = std::string("k_eo_lds<") + (sizeof(R) == 8 ? "double" : "float") + ", " +
                                      std::to_string(epi) + (sf ? ", true, " : ", false, ") +
-                                     (rec ? "true, " : "false, ") + (sf ? "false>" : "true>");
+                                     (rec ? "true, " : "false, ") + (sf || sizeof(R) == 4 ? "false>" : "true>");
             timing_end(c, ev, name, bytes);
         }
         return;
