@@ -224,7 +224,7 @@ int stencil_slots(dd_ctx* c, const Geo& g, int kind, int ncol);
 // Tuned shapes shared across processes through the file named by DD_TUNE_CACHE.
 void tune_cache_load(dd_ctx* c);
 void tune_cache_store(dd_ctx* c, const std::string& key, const StencilSched& sc);
-StencilSched default_sched(const Geo& g);
+StencilSched default_sched(const Geo& g, int kind, int ncol);
 int stencil_blocks(const Geo& g, const StencilSched& sc);
 int sched_kc(const StencilSched& sc, int ncol, size_t real_bytes, size_t col_bytes);
 int brick_rows(const Geo& g, int nt);

@@ -113,11 +113,20 @@ int brick_rows(const Geo& g, int nt) {
     return ry;
 }
 
-StencilSched default_sched(const Geo& g) {
+// Shape of a launch too small to be tuned (kind 0: FP64, 1: FP32).  A sweep over tc slices is a
+// serial chain of about 2 us a slice, so the chunks are as short as the wavefronts that run at
+// once allow: 1024 in FP64 (one a SIMD), 4096 in FP32.  Chunks of 8 slices in hardware order, and this
+// rule, us: 16 x 4^3 FP64 1 column 29.9 and 6.2; 11 x 15^3 FP32 5 columns 42.6 and 22.3; 16 x 16^3 FP64 1
+// column 42 and 16.6, 3 columns 49 and 31.6 (4 slices; 1 slice 40); 16 x 8^3 FP64 12 columns 39 and 16.7
+// (2 slices; 1 slice 19.2).  XCD-contiguous workgroups: 22.3 us against 34 for the 11 x 15^3 case.
+StencilSched default_sched(const Geo& g, int kind, int ncol) {
     StencilSched sc;
     sc.nt = 128;
-    sc.tc = g.nt < 8 ? g.nt : 8;
-    sc.remap = 0;
+    const size_t waves = (size_t)g.nsite * ncol / kWave, fit = kind == 0 ? 1024 : 4096;
+    sc.tc = 1;
+    while (sc.tc < g.nt && sc.tc < 8 && waves > fit * sc.tc) sc.tc *= 2;
+    sc.tc = sc.tc < g.nt ? sc.tc : g.nt;
+    sc.remap = 1;
     return sc;
 }
 

@@ -33,7 +33,7 @@ std::string key_of(const Geo& g, int kind, int ncol) {
 
 template <typename R>
 StencilSched tune(dd_ctx* c, const Geo& g, int ncol) {
-    StencilSched best = default_sched(g);
+    StencilSched best = default_sched(g, sizeof(R) == 8 ? 0 : 1, ncol);
     const size_t nf = (size_t)ncol * 12 * g.nsite, nl = (size_t)36 * g.vlink;
     cpx<R>*in = nullptr, *out = nullptr, *U = nullptr;
     if (hipMalloc(&in, nf * sizeof(cpx<R>)) != hipSuccess || hipMalloc(&out, nf * sizeof(cpx<R>)) != hipSuccess ||
@@ -130,7 +130,7 @@ StencilSched stencil_sched(dd_ctx* c, const Geo& g, int kind, int ncol) {
     const std::string k = key_of(g, kind, ncol);
     auto it = c->sched.find(k);
     if (it != c->sched.end()) return it->second;
-    StencilSched sc = default_sched(g);
+    StencilSched sc = default_sched(g, kind, ncol);
     if (c->autotune && (size_t)g.nsite * ncol >= ((size_t)1 << 18))
         sc = kind == 0 ? tune<double>(c, g, ncol) : tune<float>(c, g, ncol);
     tune_cache_store(c, k, sc);
