@@ -498,24 +498,21 @@ __device__ __forceinline__ void eo_tile_body(const Geo& g, const EoTile& ts, con
     }
 }
 
-// The brick of a field with x rows of L / 2 pairs and nt slices: of the shapes whose sites and
-// halo sites each fit one workgroup's 256 staging threads, the one with the least workgroups and
-// halo together (bricks at the end of an extent that they do not divide are cut short).  A time
+// The bricks of a field of L^3 x nt whose x rows have `len` staged sites: of the shapes whose sites
+// and halo sites fit one workgroup, the one with the least workgroups and halo together (bricks at the end of an extent that they do not divide are cut short).  A time
 // block of 4 bricks keeps the slices that neighbouring workgroups read in one L2.
-inline EoTile eo_tile_shape(int L, int nt) {
-    const int LH = L / 2;
+inline EoTile tile_shape(int L, int len, int nt, int sites, int halo) {
     EoTile best{1, 1, 1, nt, L, L, 1};
     double score = 1e30;
     for (int ry = 1; ry <= L; ry++)
         for (int rz = 1; rz <= L; rz++) {
-            const int sl = ry * rz * LH, hr = ((ry < L ? 2 * rz : 0) + (rz < L ? 2 * ry : 0)) * LH;
-            if (sl > kTileSites || hr > kTileSites) continue;
-            int rt = kTileSites / sl;
-            if (hr > 0 && kTileSites / hr < rt) rt = kTileSites / hr;
+            const int sl = ry * rz * len, hr = ((ry < L ? 2 * rz : 0) + (rz < L ? 2 * ry : 0)) * len;
+            if (sl > sites || hr > halo) continue;
+            int rt = sites / sl;
+            if (hr > 0 && halo / hr < rt) rt = halo / hr;
             if (rt > nt) rt = nt;
             const int nty = (L + ry - 1) / ry, ntz = (L + rz - 1) / rz, ntt = (nt + rt - 1) / rt;
-            const double wg = (double)nty * ntz * ntt;
-            const double sc = wg * (kTileSites + 0.5 * hr * rt);
+            const double sc = (double)nty * ntz * ntt * (sites + 0.5 * hr * rt);
             if (sc < score) {
                 score = sc;
                 best = EoTile{rt, ry, rz, ntt, nty, ntz, 1};
@@ -524,6 +521,7 @@ inline EoTile eo_tile_shape(int L, int nt) {
     best.tb = best.ntt < 4 ? best.ntt : 4;
     return best;
 }
+inline EoTile eo_tile_shape(int L, int nt) { return tile_shape(L, L / 2, nt, kTileSites, kTileSites); }
 inline int eo_tile_blocks(const EoTile& t) { return t.ntt * t.nty * t.ntz; }
 
 }  // namespace dd

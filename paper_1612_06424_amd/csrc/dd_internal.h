@@ -124,8 +124,8 @@ struct StencilSched {
     int blocked = 0;  // tile flags: bit 0 tiles as (y, z) bricks of x rows (even-odd: 4 x 4),
                       // bit 1 the time chunks of a tile in adjacent workgroups, bit 2 non-temporal
                       // output stores (half hop, two columns per thread) or, for the full stencil,
-                      // x hops loaded rather than taken from neighbouring lanes; bit 3 the half
-                      // hop's LDS-tile form
+                      // x hops loaded rather than taken from neighbouring lanes; bit 3 the
+                      // LDS-tile form (kc: columns per workgroup)
 };
 
 struct TimedLaunch {
@@ -232,6 +232,14 @@ template <typename R>
 void launch_dslash_sched(dd_ctx* c, const Geo& g, const StencilSched& sc, const cpx<R>* U, double kappa,
                          int dag, int epi, const cpx<R>* in, cpx<R>* out, const cpx<R>* aux, int ncol,
                          double* partial, const ColState* st);
+// The stencil's LDS-tile form (dirac_tile.hip), tile flag bit 3 of a schedule with kc columns per
+// workgroup: usable on fields whose column is below 2 GiB; its partial slots per column.
+bool dslash_lds_ok(const Geo& g, size_t real_bytes);
+int dslash_lds_blocks(const Geo& g);
+template <typename R>
+void launch_dslash_lds(dd_ctx* c, const Geo& g, const StencilSched& sc, const cpx<R>* U, R mass, int dag, int epi,
+                       const cpx<R>* in, cpx<R>* out, const cpx<R>* aux, int ncol, double* partial,
+                       const ColState* st);
 inline int site_blocks(int nsite) { return (nsite + kBlock - 1) / kBlock; }
 
 // ---------------------------------------------------------------- solver segments

@@ -131,6 +131,7 @@ StencilSched default_sched(const Geo& g, int kind, int ncol) {
 }
 
 int stencil_blocks(const Geo& g, const StencilSched& sc) {
+    if (sc.blocked & 8) return dslash_lds_blocks(g);
     const int nsb = (g.L3 + sc.nt - 1) / sc.nt;
     const int nchunk = (g.nt + sc.tc - 1) / sc.tc;
     return nsb * nchunk;
@@ -140,13 +141,24 @@ template <typename R>
 void launch_dslash_sched(dd_ctx* c, const Geo& g, const StencilSched& sc, const cpx<R>* U, double kappa,
                          int dag, int epi, const cpx<R>* in, cpx<R>* out, const cpx<R>* aux, int ncol,
                          double* partial, const ColState* st) {
+    const R mass = R(epi == EPI_HOP ? kappa : 1.0 / (2.0 * kappa));  // EPI_HOP scales the hop by kappa
+    const double extra = (epi == EPI_DOT_AUX || epi == EPI_RESID) ? 24.0 : 0.0;
+    const double bytes = (double)g.nsite * ((48.0 + extra) * ncol * c->bill_frac + 72.0) * sizeof(R);
+    if (sc.blocked & 8) {
+        hipEvent_t ev = nullptr;
+        if (c->timing) timing_begin(c, &ev);
+        launch_dslash_lds<R>(c, g, sc, U, mass, dag, epi, in, out, aux, ncol, partial, st);
+        if (c->timing)
+            timing_end(c, ev, std::string("k_dslash_lds<") + (sizeof(R) == 8 ? "double" : "float") + ", " +
+                                  std::to_string(epi) + ">", bytes);
+        return;
+    }
     const int kc = sched_kc(sc, ncol, sizeof(R), (size_t)12 * g.nsite * sizeof(cpx<R>));
     const dim3 grid((unsigned)stencil_blocks(g, sc) * (unsigned)(ncol / kc));
     // tile flags as the kernel reads them: bit 0 bricks (with the brick's y rows in bits 8+),
     // bit 1 chunk-adjacent order
     const int ry = brick_rows(g, sc.nt);
     const int blk = ((sc.blocked & 1) && ry > 0 ? 1 | (ry << 8) : 0) | (sc.blocked & 2);
-    const R mass = R(epi == EPI_HOP ? kappa : 1.0 / (2.0 * kappa));  // EPI_HOP scales the hop by kappa
     // x hops through lane permutes where every wavefront holds whole x rows (NT is 128 or 256),
     // unless tile flag bit 2 asks for the loading form (never set by the tuner)
     const bool xs = g.L >= 4 && kWave % g.L == 0 && (sc.blocked & 4) == 0;
@@ -170,8 +182,6 @@ void launch_dslash_sched(dd_ctx* c, const Geo& g, const StencilSched& sc, const 
 #undef DD_NT_CASE
 #undef DD_KC_CASE
     if (c->timing) {
-        const double extra = (epi == EPI_DOT_AUX || epi == EPI_RESID) ? 24.0 : 0.0;
-        const double bytes = (double)g.nsite * ((48.0 + extra) * ncol * c->bill_frac + 72.0) * sizeof(R);
         const std::string name = std::string("k_dslash<") + (sizeof(R) == 8 ? "double" : "float") + ", " +
                                  std::to_string(dag ? 1 : 0) + ", " + std::to_string(epi) + ", " +
                                  std::to_string(sc.nt) + (kc > 1 ? ", " + std::to_string(kc) : std::string()) + ">";
