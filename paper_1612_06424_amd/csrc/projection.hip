@@ -12,7 +12,7 @@
 // R^+ R, V <- V R^-1.  Vectors are [N_m][n] complex128 (n = 12 x sites of the
 // field, components outermost as in every field of the library).  The Gram
 // matrix is summed from fixed per-workgroup partials in a fixed order, so the
-// result is reproducible run to run.
+// result is reproducible run to run.  Gram matrix and combination run on the FP64 matrix cores.
 #include <algorithm>
 #include <chrono>
 #include <cmath>
@@ -25,138 +25,267 @@ namespace dd {
 
 namespace {
 
-constexpr int kGT = 16;       // Gram tile: kGT x kGT outputs per workgroup (256 threads)
-constexpr int kGR = 64;       // rows staged in LDS per step
-constexpr int kGChunk = 8192; // rows per workgroup (one partial)
-constexpr int kCB = 16;       // output columns per workgroup of the combine kernel
+typedef double dbl4 __attribute__((ext_vector_type(4)));
+
+constexpr int kGT = 32;          // Gram tile: kGT x kGT outputs (2 x 2 matrix-core blocks) per workgroup
+constexpr int kGThreads = 512;   // eight wavefronts, each 16 of every 128 rows
+constexpr int kGBlocks = 512;    // workgroups aimed at: two per CU
+constexpr int kCB = 32;          // output columns per workgroup of the combine kernel
+constexpr int kCP = 64;          // rows of the small matrix staged in LDS at a time
+constexpr int kCR = 2;           // blocks of 16 rows per wavefront of the combine kernel
+constexpr int kCholLds = 64;     // largest matrix factorised in LDS
 
 __device__ inline cpx<double> cj(cpx<double> a) { return {a.re, -a.im}; }
 
-// Gp[chunk][a][b] = sum over the chunk's rows i of conj(A[a][i]) B[b][i]
-// (tile (ta, tb) of kGT x kGT; with sym only the tiles ta <= tb).
-__global__ __launch_bounds__(256) void k_xgram_partial(int na, int nb, long long n, const cpx<double>* __restrict__ A,
-                                                       const cpx<double>* __restrict__ B, int sym,
-                                                       cpx<double>* __restrict__ Gp) {
-    const int ta = blockIdx.x, tb = blockIdx.y, chunk = blockIdx.z;
-    if (sym && ta > tb) return;  // uniform over the workgroup
-    __shared__ cpx<double> sa[kGT][kGR + 1], sb[kGT][kGR + 1];
-    const int tid = threadIdx.x;
-    const int ia = tid / kGT, ib = tid % kGT;
-    const long long r0 = (long long)chunk * kGChunk;
-    const long long r1 = std::min(n, r0 + kGChunk);
-    cpx<double> acc = {0.0, 0.0};
-    for (long long base = r0; base < r1; base += kGR) {
-        // stage kGT rows of A and of B, kGR entries each (zeros past the ends)
-        for (int e = tid; e < kGT * kGR; e += 256) {
-            const int v = e / kGR, r = e % kGR;
-            const long long i = base + r;
-            const int a = ta * kGT + v, b = tb * kGT + v;
-            sa[v][r] = (a < na && i < r1) ? A[(size_t)a * n + i] : cpx<double>{0.0, 0.0};
-            sb[v][r] = (b < nb && i < r1) ? B[(size_t)b * n + i] : cpx<double>{0.0, 0.0};
-        }
-        __syncthreads();
-#pragma unroll 8
-        for (int r = 0; r < kGR; r++) acc = acc + cj(sa[ia][r]) * sb[ib][r];
-        __syncthreads();
-    }
-    const int a = ta * kGT + ia, b = tb * kGT + ib;
-    if (a < na && b < nb) Gp[((size_t)chunk * na + a) * nb + b] = acc;
+// v_mfma_f64_16x16x4f64: a 16 x 4 block (lane l holds A[l % 16][l / 16]) times a 4 x 16 block (lane l
+// holds B[l / 16][l % 16]) into a 16 x 16 accumulator (lane l holds rows l / 16 + 4 e, e = 0..3, of
+// column l % 16).
+__device__ __forceinline__ dbl4 mfma(double a, double b, dbl4 c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
-// G[a][b] = sum of the partials in chunk order; with sym the lower triangle is
-// the conjugate of the upper one.
+// One workgroup's tile of a Gram partial: TA x TB blocks of 16 x 16 over the rows [r0, r1).  DIAG: A
+// and B are the same vectors (TA = TB, the block below the diagonal left out).  A wavefront takes 16 rows
+// per step: lane l holds rows base + l / 16 + 4 j (j = 0..3) of vector l % 16 of each block, so a load is
+// 64 contiguous bytes of each of 16 vectors, and the four MFMAs of a row quartet contract them.  Vectors
+// past the end repeat the last one (their outputs are not stored); rows past r1 count as zero.
+template <bool DIAG, int TA, int TB>
+__device__ __forceinline__ void xgram_tile(int a0, int b0, int na, int nb, long long n, long long r0, long long r1,
+                                           const cpx<double>* __restrict__ A, const cpx<double>* __restrict__ B,
+                                           cpx<double>* __restrict__ Gp, double (*sh)[512]) {
+    const int tid = (int)threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const cpx<double>*pa[TA], *pb[TB];
+#pragma unroll
+    for (int t = 0; t < TA; t++) pa[t] = A + (size_t)min(a0 + t * 16 + (lane & 15), na - 1) * n;
+#pragma unroll
+    for (int t = 0; t < TB; t++) pb[t] = B + (size_t)min(b0 + t * 16 + (lane & 15), nb - 1) * n;
+    dbl4 re[TA][TB], im[TA][TB];
+#pragma unroll
+    for (int t = 0; t < TA; t++)
+#pragma unroll
+        for (int u = 0; u < TB; u++) re[t][u] = im[t][u] = dbl4{0.0, 0.0, 0.0, 0.0};
+    constexpr int kStep = 16 * (kGThreads / 64);
+    for (long long base = r0 + wv * 16; base < r1; base += kStep) {
+        cpx<double> va[TA][4], vb[TB][4];
+#pragma unroll
+        for (int j = 0; j < 4; j++) {
+            const long long i = base + (lane >> 4) + 4 * j;
+            const bool ok = i < r1;
+            const long long ic = ok ? i : r0;
+#pragma unroll
+            for (int t = 0; t < TA; t++) {
+                va[t][j] = pa[t][ic];
+                if (!ok) va[t][j] = cpx<double>{0.0, 0.0};
+            }
+            if constexpr (!DIAG) {
+#pragma unroll
+                for (int t = 0; t < TB; t++) {
+                    vb[t][j] = pb[t][ic];
+                    if (!ok) vb[t][j] = cpx<double>{0.0, 0.0};
+                }
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < 4; j++)
+#pragma unroll
+            for (int t = 0; t < TA; t++)
+#pragma unroll
+                for (int u = 0; u < TB; u++) {
+                    if (DIAG && u < t) continue;
+                    const cpx<double> x = va[t][j], y = DIAG ? va[u][j] : vb[u][j];
+                    re[t][u] = mfma(x.re, y.re, re[t][u]);
+                    im[t][u] = mfma(x.re, y.im, im[t][u]);
+                    re[t][u] = mfma(x.im, y.im, re[t][u]);
+                    im[t][u] = mfma(-x.im, y.re, im[t][u]);
+                }
+    }
+    // the eight wavefronts' sums, in wavefront order
+#pragma unroll
+    for (int t = 0; t < TA; t++)
+#pragma unroll
+        for (int u = 0; u < TB; u++) {
+            if (DIAG && u < t) continue;
+#pragma unroll
+            for (int e = 0; e < 4; e++) {
+                sh[wv][((e * 4 + (lane >> 4)) * 16 + (lane & 15)) * 2] = re[t][u][e];
+                sh[wv][((e * 4 + (lane >> 4)) * 16 + (lane & 15)) * 2 + 1] = im[t][u][e];
+            }
+            __syncthreads();
+            double s = 0;
+#pragma unroll
+            for (int w = 0; w < kGThreads / 64; w++) s += sh[w][tid];
+            const int a = a0 + t * 16 + tid / 32, b = b0 + u * 16 + (tid / 2) % 16;
+            if (a < na && b < nb) reinterpret_cast<double*>(Gp + (size_t)a * nb + b)[tid & 1] = s;
+            __syncthreads();
+        }
+}
+
+// Gp[chunk][a][b] = sum over the chunk's `rows` rows i of conj(A[a][i]) B[b][i] (tile (ta, tb) of
+// kGT x kGT; with sym, A = B, only the tiles ta <= tb).  The vectors are read once per tile, which bounds
+// the time up to 32 vectors (one tile); the products take 15 us on the FP64 matrix cores.  24
+// vectors, four calls of 8 x 16^3 and six of one slice: 36 us on average; products of scalars from LDS, a
+// 16 x 16 tile and 8192 rows per workgroup, took 490.
+__global__ __launch_bounds__(kGThreads, 2) void k_xgram_partial(int na, int nb, long long n, long long rows,
+                                                                const cpx<double>* __restrict__ A,
+                                                                const cpx<double>* __restrict__ B, int sym,
+                                                                cpx<double>* __restrict__ Gp) {
+    const int ta = blockIdx.x, tb = blockIdx.y, chunk = blockIdx.z;
+    if (sym && ta > tb) return;  // uniform over the workgroup
+    const long long r0 = (long long)chunk * rows, r1 = std::min(n, r0 + rows);
+    __shared__ double sh[kGThreads / 64][512];
+    const int a0 = ta * kGT, b0 = tb * kGT;
+    Gp += (size_t)chunk * na * nb;
+    const bool a1 = na - a0 <= 16, b1 = nb - b0 <= 16;  // one block of vectors is enough
+    if (sym && ta == tb) {
+        if (a1)
+            xgram_tile<true, 1, 1>(a0, b0, na, nb, n, r0, r1, A, B, Gp, sh);
+        else
+            xgram_tile<true, 2, 2>(a0, b0, na, nb, n, r0, r1, A, B, Gp, sh);
+    } else if (b1) {
+        if (a1)
+            xgram_tile<false, 1, 1>(a0, b0, na, nb, n, r0, r1, A, B, Gp, sh);
+        else
+            xgram_tile<false, 2, 1>(a0, b0, na, nb, n, r0, r1, A, B, Gp, sh);
+    } else {
+        xgram_tile<false, 2, 2>(a0, b0, na, nb, n, r0, r1, A, B, Gp, sh);
+    }
+}
+
+// G[a][b] = sum of the partials (chunks k, k + 16, .. by thread k of 16, then those in order); with sym
+// the lower triangle is the conjugate of the upper one.  16 entries per workgroup.
 __global__ __launch_bounds__(256) void k_xgram_reduce(int na, int nb, int nchunk, int sym,
                                                       const cpx<double>* __restrict__ Gp, cpx<double>* __restrict__ G) {
-    const int e = blockIdx.x * 256 + threadIdx.x;
-    if (e >= na * nb) return;
-    const int a = e / nb, b = e % nb;
+    __shared__ cpx<double> sh[16][17];
+    const int le = threadIdx.x & 15, lc = threadIdx.x >> 4;
+    const int e = blockIdx.x * 16 + le;
+    const bool ok = e < na * nb;
+    const int a = ok ? e / nb : 0, b = ok ? e % nb : 0;
     const int ua = sym && a > b ? b : a, ub = sym && a > b ? a : b;
     cpx<double> s = {0.0, 0.0};
-    for (int c = 0; c < nchunk; c++) s = s + Gp[((size_t)c * na + ua) * nb + ub];
+#pragma unroll 8
+    for (int c = lc; c < nchunk; c += 16) s = s + Gp[((size_t)c * na + ua) * nb + ub];
+    sh[lc][le] = s;
+    __syncthreads();
+    if (lc != 0 || !ok) return;
+    for (int k = 1; k < 16; k++) s = s + sh[k][le];
     G[e] = (sym && a > b) ? cj(s) : s;
 }
 
-// R entries written by other threads of the workgroup are read around the
-// vector L1 cache (volatile: from L2), after the barrier that orders the writes.
-__device__ inline cpx<double> ldv(const cpx<double>* p) {
-    const volatile double* q = (const volatile double*)p;
-    return {q[0], q[1]};
-}
-
-// One workgroup: G = R^+ R (R upper triangular, positive real diagonal), then
-// Rinv = R^-1 (upper triangular, zeros below the diagonal).  flag = 1 if a pivot
-// is not positive and finite (the vectors are linearly dependent in FP64).
-__global__ __launch_bounds__(256) void k_chol_inv(int n, const cpx<double>* __restrict__ G, cpx<double>* R,
-                                                  cpx<double>* __restrict__ Rinv, int* __restrict__ flag) {
-    const int tid = threadIdx.x;
-    __shared__ double piv;
-    __shared__ int bad;
-    if (tid == 0) bad = 0;
-    for (int e = tid; e < n * n; e += 256) R[e] = cpx<double>{0.0, 0.0};
+// One workgroup: G = R^+ R (R upper triangular, positive real diagonal), then Rinv = R^-1 (upper
+// triangular, zeros below the diagonal).  flag = 1 if a pivot is not positive and finite (the vectors are
+// linearly dependent in FP64).  Row elimination of [G | 1] in place: after step k, row k holds
+// L^-1 = (R^-1)^+ up to column k and R behind it, and the rows below are updated by all threads at
+// once, so the serial chain is n steps of two barriers (24 vectors: 15 us; pivots and rows computed from
+// global memory one after the other, 255).  M is in LDS up to kCholLds vectors, in global memory above.
+__device__ __forceinline__ void chol_inv(int n, cpx<double>* M, const cpx<double>* __restrict__ G,
+                                         cpx<double>* __restrict__ Rinv, int* __restrict__ flag) {
+    const int tid = (int)threadIdx.x, nth = (int)blockDim.x;
+    bool bad = false;  // the same in every thread
+    for (int e = tid; e < n * n; e += nth) M[e] = G[e];
     __syncthreads();
     for (int k = 0; k < n; k++) {
-        if (tid == 0) {
-            double d = G[(size_t)k * n + k].re;
-            for (int j = 0; j < k; j++) {
-                const cpx<double> r = ldv(&R[(size_t)j * n + k]);
-                d -= r.re * r.re + r.im * r.im;
-            }
-            if (!(d > 0.0) || !std::isfinite(d)) {
-                bad = 1;
-                d = 1.0;
-            }
-            piv = sqrt(d);
-            R[(size_t)k * n + k] = cpx<double>{piv, 0.0};
+        double d = M[(size_t)k * n + k].re;
+        if (!(d > 0.0) || !std::isfinite(d)) {
+            bad = true;
+            d = 1.0;
+        }
+        const double inv = 1.0 / sqrt(d);
+        __syncthreads();  // the pivot has been read
+        for (int c = tid; c < n; c += nth) {
+            const cpx<double> v = M[(size_t)k * n + c];
+            M[(size_t)k * n + c] = c == k ? cpx<double>{inv, 0.0} : cpx<double>{v.re * inv, v.im * inv};
         }
         __syncthreads();
-        for (int b = k + 1 + tid; b < n; b += 256) {
-            cpx<double> s = G[(size_t)k * n + b];
-            for (int j = 0; j < k; j++) s = s - cj(ldv(&R[(size_t)j * n + k])) * ldv(&R[(size_t)j * n + b]);
-            R[(size_t)k * n + b] = cpx<double>{s.re / piv, s.im / piv};
+        for (int e = tid; e < (n - k - 1) * n; e += nth) {
+            const int i = k + 1 + e / n, c = e % n;
+            if (c > k && c < i) continue;  // below the diagonal of what is left of G: never read
+            const cpx<double> f = cj(M[(size_t)k * n + i]);  // R[k][i]^*
+            const cpx<double> v = c == k ? cpx<double>{0.0, 0.0} : M[(size_t)i * n + c];
+            M[(size_t)i * n + c] = v - f * M[(size_t)k * n + c];
         }
         __syncthreads();
     }
-    // back substitution, one column of Rinv per thread
-    for (int j = tid; j < n; j += 256) {
-        for (int i = n - 1; i >= 0; i--) {
-            if (i > j) {
-                Rinv[(size_t)i * n + j] = cpx<double>{0.0, 0.0};
-                continue;
-            }
-            cpx<double> s = {i == j ? 1.0 : 0.0, 0.0};
-            for (int k = i + 1; k <= j; k++) s = s - ldv(&R[(size_t)i * n + k]) * Rinv[(size_t)k * n + j];
-            const double d = ldv(&R[(size_t)i * n + i]).re;
-            Rinv[(size_t)i * n + j] = cpx<double>{s.re / d, s.im / d};
-        }
+    for (int e = tid; e < n * n; e += nth) {
+        const int i = e / n, j = e % n;  // R^-1[i][j] = (L^-1[j][i])^*
+        Rinv[e] = i <= j ? cj(M[(size_t)j * n + i]) : cpx<double>{0.0, 0.0};
     }
-    __syncthreads();
     if (tid == 0 && bad) flag[0] = 1;
 }
+__global__ __launch_bounds__(512) void k_chol_inv(int n, const cpx<double>* __restrict__ G,
+                                                  cpx<double>* __restrict__ Rinv, int* __restrict__ flag) {
+    __shared__ cpx<double> M[kCholLds * kCholLds];
+    chol_inv(n, M, G, Rinv, flag);
+}
+__global__ __launch_bounds__(1024) void k_chol_inv_global(int n, const cpx<double>* __restrict__ G, cpx<double>* M,
+                                                          cpx<double>* __restrict__ Rinv, int* __restrict__ flag) {
+    chol_inv(n, M, G, Rinv, flag);
+}
 
-// out[b][i] = sum_a A[a][i] M[a][b] for the kCB columns b of this workgroup;
-// M (na x nb) staged in LDS.
+// out[b][i] = sum_a A[a][i] M[a][b] for the kCB columns b of this workgroup (with tri, M is upper
+// triangular).  M (na x nb) goes through LDS kCP rows at a time; a wavefront owns kCR blocks of 16 rows i
+// and both blocks of 16 columns, so up to 32 columns A is read once, and a load or store is 256 contiguous
+// bytes.  Bound by its two passes over the vectors: 24 vectors, four calls of 8 x 16^3 and six of one slice, 41 us
+// on average (products of scalars, 16 columns per workgroup: 68).
 __global__ __launch_bounds__(256) void k_combine(int na, int nb, long long n, const cpx<double>* __restrict__ A,
-                                                 const cpx<double>* __restrict__ M, cpx<double>* __restrict__ out) {
-    __shared__ cpx<double> sm[kMaxProjVec][kCB];
+                                                 const cpx<double>* __restrict__ M, int tri,
+                                                 cpx<double>* __restrict__ out) {
+    __shared__ cpx<double> sm[kCP][kCB + 1];
+    const int lane = (int)threadIdx.x & 63, wv = (int)threadIdx.x >> 6;
     const int b0 = blockIdx.y * kCB;
-    for (int e = threadIdx.x; e < na * kCB; e += 256) {
-        const int a = e / kCB, j = e % kCB;
-        sm[a][j] = (b0 + j < nb) ? M[(size_t)a * nb + b0 + j] : cpx<double>{0.0, 0.0};
+    const bool two = nb - b0 > 16;  // uniform over the workgroup
+    const long long i0 = ((long long)blockIdx.x * 4 + wv) * (16 * kCR) + (lane & 15);
+    long long ic[kCR];
+#pragma unroll
+    for (int r = 0; r < kCR; r++) ic[r] = std::min(i0 + 16 * r, n - 1);
+    dbl4 re[2][kCR], im[2][kCR];
+#pragma unroll
+    for (int t = 0; t < 2; t++)
+#pragma unroll
+        for (int r = 0; r < kCR; r++) re[t][r] = im[t][r] = dbl4{0.0, 0.0, 0.0, 0.0};
+    const int ka = tri ? std::min(na, b0 + kCB) : na;
+    for (int p0 = 0; p0 < ka; p0 += kCP) {
+        const int np = std::min(kCP, ka - p0), np4 = (np + 3) & ~3;
+        if (p0) __syncthreads();  // the panel before has been used
+        for (int e = threadIdx.x; e < np4 * kCB; e += 256) {
+            const int a = e / kCB, j = e % kCB;
+            sm[a][j] = (a < np && b0 + j < nb) ? M[(size_t)(p0 + a) * nb + b0 + j] : cpx<double>{0.0, 0.0};
+        }
+        __syncthreads();
+#pragma unroll 4
+        for (int a = 0; a < np4; a += 4) {
+            const int al = a + (lane >> 4);
+            const bool ok = al < np;
+            const cpx<double>* row = A + (size_t)(p0 + (ok ? al : 0)) * n;
+            cpx<double> v[kCR];
+#pragma unroll
+            for (int r = 0; r < kCR; r++) {
+                v[r] = row[ic[r]];
+                if (!ok) v[r] = cpx<double>{0.0, 0.0};  // (an infinity of another vector must not meet a zero of M)
+            }
+#pragma unroll
+            for (int t = 0; t < 2; t++) {
+                if (t == 1 && !two) break;
+                const cpx<double> m = sm[al][t * 16 + (lane & 15)];
+#pragma unroll
+                for (int r = 0; r < kCR; r++) {
+                    re[t][r] = mfma(m.re, v[r].re, re[t][r]);
+                    im[t][r] = mfma(m.re, v[r].im, im[t][r]);
+                    re[t][r] = mfma(-m.im, v[r].im, re[t][r]);
+                    im[t][r] = mfma(m.im, v[r].re, im[t][r]);
+                }
+            }
+        }
     }
-    __syncthreads();
-    const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    cpx<double> acc[kCB];
 #pragma unroll
-    for (int j = 0; j < kCB; j++) acc[j] = cpx<double>{0.0, 0.0};
-    for (int a = 0; a < na; a++) {
-        const cpx<double> v = A[(size_t)a * n + i];
+    for (int t = 0; t < 2; t++)
 #pragma unroll
-        for (int j = 0; j < kCB; j++) acc[j] = acc[j] + v * sm[a][j];
-    }
+        for (int r = 0; r < kCR; r++)
 #pragma unroll
-    for (int j = 0; j < kCB; j++)
-        if (b0 + j < nb) out[(size_t)(b0 + j) * n + i] = acc[j];
+            for (int e = 0; e < 4; e++) {
+                const int b = b0 + t * 16 + (lane >> 4) + 4 * e;
+                const long long i = i0 + 16 * r;
+                if (b < nb && i < n) out[(size_t)b * n + i] = cpx<double>{re[t][r][e], im[t][r][e]};
+            }
 }
 
 // W[a][c][s] = ((1 + SGN gamma_0)/2 V[a] on slice k of the slab)_c(s)
@@ -178,22 +307,29 @@ __global__ __launch_bounds__(256) void k_slice_project(int nvec, int L3, int nsi
     for (int c = 0; c < 12; c++) W[((size_t)a * 12 + c) * L3 + s] = cpx<double>{0.5 * o[c].re, 0.5 * o[c].im};
 }
 
-int gram_chunks(long long n) { return (int)((n + kGChunk - 1) / kGChunk); }
+// Partials of a Gram matrix: as many as fill kGBlocks workgroups, each of at least one step of rows.
+int gram_max_chunks(int na, int nb) {
+    return std::max(1, kGBlocks / (((na + kGT - 1) / kGT) * ((nb + kGT - 1) / kGT)));
+}
 
-// G = A^+ B (na x nb); Gp: nchunk x na x nb scratch
+// G = A^+ B (na x nb); Gp: gram_max_chunks x na x nb scratch
 void launch_xgram(dd_ctx* c, int na, int nb, long long n, const cpx<double>* A, const cpx<double>* B, bool sym,
                   cpx<double>* Gp, cpx<double>* G) {
-    const int nchunk = gram_chunks(n);
+    const long long step = 16 * (kGThreads / 64), want = gram_max_chunks(na, nb);
+    const long long rows = ((n + want - 1) / want + step - 1) / step * step;
+    const int nchunk = (int)((n + rows - 1) / rows);
     const dim3 grid((unsigned)((na + kGT - 1) / kGT), (unsigned)((nb + kGT - 1) / kGT), (unsigned)nchunk);
-    hipLaunchKernelGGL(k_xgram_partial, grid, dim3(256), 0, c->stream, na, nb, n, A, B, sym ? 1 : 0, Gp);
-    hipLaunchKernelGGL(k_xgram_reduce, dim3((unsigned)((na * nb + 255) / 256)), dim3(256), 0, c->stream, na, nb,
+    hipLaunchKernelGGL(k_xgram_partial, grid, dim3(kGThreads), 0, c->stream, na, nb, n, rows, A, B,
+                       sym ? 1 : 0, Gp);
+    hipLaunchKernelGGL(k_xgram_reduce, dim3((unsigned)((na * nb + 15) / 16)), dim3(256), 0, c->stream, na, nb,
                        nchunk, sym ? 1 : 0, Gp, G);
 }
 
-void launch_combine(dd_ctx* c, int na, int nb, long long n, const cpx<double>* A, const cpx<double>* M,
+void launch_combine(dd_ctx* c, int na, int nb, long long n, const cpx<double>* A, const cpx<double>* M, bool tri,
                     cpx<double>* out) {
-    const dim3 grid((unsigned)((n + 255) / 256), (unsigned)((nb + kCB - 1) / kCB));
-    hipLaunchKernelGGL(k_combine, grid, dim3(256), 0, c->stream, na, nb, n, A, M, out);
+    const long long per = 4 * 16 * kCR;
+    const dim3 grid((unsigned)((n + per - 1) / per), (unsigned)((nb + kCB - 1) / kCB));
+    hipLaunchKernelGGL(k_combine, grid, dim3(256), 0, c->stream, na, nb, n, A, M, tri ? 1 : 0, out);
 }
 
 struct OrthoWork {
@@ -204,10 +340,11 @@ struct OrthoWork {
     int* flag;
 };
 
-dd_status ortho_work(dd_ctx* c, int nvec, long long n, OrthoWork* w) {
+// scratch of Gram matrices na x nb
+dd_status ortho_work(dd_ctx* c, int na, int nb, OrthoWork* w) {
     dd_status e = DD_OK;
-    const size_t nn = (size_t)nvec * nvec;
-    w->Gp = (cpx<double>*)workspace(c, W_PROJ_G, (size_t)gram_chunks(n) * nn * sizeof(cpx<double>), &e);
+    const size_t nn = (size_t)na * nb;
+    w->Gp = (cpx<double>*)workspace(c, W_PROJ_G, (size_t)gram_max_chunks(na, nb) * nn * sizeof(cpx<double>), &e);
     if (e != DD_OK) return e;
     cpx<double>* m = (cpx<double>*)workspace(c, W_PROJ_R, (3 * nn + 1) * sizeof(cpx<double>), &e);
     if (e != DD_OK) return e;
@@ -224,8 +361,11 @@ void orthonormalize(dd_ctx* c, int nvec, long long n, cpx<double>* V, cpx<double
         cpx<double>* src = pass == 0 ? V : tmp;
         cpx<double>* dst = pass == 0 ? tmp : V;
         launch_xgram(c, nvec, nvec, n, src, src, true, w.Gp, w.G);
-        hipLaunchKernelGGL(k_chol_inv, dim3(1), dim3(256), 0, c->stream, nvec, w.G, w.R, w.Rinv, w.flag);
-        launch_combine(c, nvec, nvec, n, src, w.Rinv, dst);
+        if (nvec <= kCholLds)
+            hipLaunchKernelGGL(k_chol_inv, dim3(1), dim3(512), 0, c->stream, nvec, w.G, w.Rinv, w.flag);
+        else
+            hipLaunchKernelGGL(k_chol_inv_global, dim3(1), dim3(1024), 0, c->stream, nvec, w.G, w.R, w.Rinv, w.flag);
+        launch_combine(c, nvec, nvec, n, src, w.Rinv, true, dst);
     }
 }
 
@@ -247,7 +387,7 @@ dd_status projection_basis(dd_ctx* c, const cpx<double>* U, double kappa, const 
     if (e != DD_OK) return e;
     cpx<double>* Vt = V + (size_t)nvec * n;
     OrthoWork w;
-    if ((e = ortho_work(c, nvec, n, &w)) != DD_OK) return e;
+    if ((e = ortho_work(c, nvec, nvec, &w)) != DD_OK) return e;
     DD_HIP(c, hipMemsetAsync(w.flag, 0, sizeof(int), c->stream));
     DD_HIP(c, hipMemcpyAsync(V, v0, (size_t)nvec * n * sizeof(cpx<double>), hipMemcpyDeviceToDevice, c->stream));
     orthonormalize(c, nvec, n, V, Vt, w);
@@ -303,10 +443,10 @@ dd_status project_slice(dd_ctx* c, int L3, int nt, int k, int ncol, cpx<double>*
     if (e != DD_OK) return e;
     cpx<double>* out = buf + (size_t)ncol * ns;
     OrthoWork w;
-    if ((e = ortho_work(c, std::max(nvec, ncol), ns, &w)) != DD_OK) return e;
+    if ((e = ortho_work(c, nvec, ncol, &w)) != DD_OK) return e;
     launch_slab_embed(c, L3, nt, k, 1, ncol, buf, field, 1);        // the slice, [ncol][12][L3]
     launch_xgram(c, nvec, ncol, ns, phi, buf, false, w.Gp, w.G);    // C = phi^+ field (nvec x ncol)
-    launch_combine(c, nvec, ncol, ns, phi, w.G, out);                // phi C
+    launch_combine(c, nvec, ncol, ns, phi, w.G, false, out);                // phi C
     launch_slab_embed(c, L3, nt, k, 1, ncol, out, field, 0);
     DD_HIP(c, hipGetLastError());
     return DD_OK;
