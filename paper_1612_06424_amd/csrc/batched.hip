@@ -723,9 +723,12 @@ dd_status solve_batch_eo(dd_ctx* c, const std::vector<Item>& its, const dd_solve
                 for (int kc : {1, 2})
                     for (int bl = 0; bl < (any4 ? 2 : 1); bl++)
                         if (e == DD_OK && kc_ok(kc)) e = try_shape(t, kc, bl, 0);
-            // the LDS-tile form, the columns of a domain in 1 to 3 groups
-            for (int kc : {12, 6, 4})
-                if (e == DD_OK) e = try_shape(1, kc, 8, 1);
+            // the LDS-tile form, a domain's columns in 1 to 3 groups or, for batches that leave the chip
+            // idle, two and one by one
+            int widest = 0;
+            for (const Item& it : its) widest = std::max(widest, it.ncol);
+            for (int kc : {12, 6, 4, 2, 1})
+                if (e == DD_OK && (kc <= widest || kc == 12)) e = try_shape(1, kc, 8, 1);
             c->timing = saved;
             S.nblk = 0;  // launches size themselves from nblk64 / nblk32 again
             (void)hipEventDestroy(ea);

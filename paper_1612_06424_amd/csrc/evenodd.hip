@@ -195,16 +195,34 @@ StencilSched eo_tile_sched(int ncol, int parts) {
     return sc;
 }
 
-// The shape of a launch that is not tuned.  The LDS-tile form needs a workgroup per CU with columns
-// to loop over (FP64, 12 columns: 16 x 32^3, 1024 bricks, 418 us against the sweep's 579; 32 x 16^3, 256
-// bricks, 86 against 140; 8 x 16^3, 64 bricks, 36 against 31).  Below that the sweep of one slice per chunk,
-// one column per thread: the most workgroups and the shortest serial chain (one column on
-// 32 x 16^3, chunks of 1 and 4 slices: FP32 10.5 and 25 us, FP64 17.7 and 36).
-StencilSched eo_default_sched(const Geo& g, int ncol) {
-    if (ncol >= 4 && eo_tile_blocks(eo_tile_shape(g.L, g.nt)) >= 256) return eo_tile_sched(ncol, 1);
+// Columns per workgroup of the LDS-tile form that leave about one workgroup per CU.
+int eo_tile_cols(const Geo& g, int ncol) {
+    const int tiles = eo_tile_blocks(eo_tile_shape(g.L, g.nt));
+    return std::max(1, std::min(ncol, (int)(((size_t)ncol * tiles + 255) / 256)));
+}
+
+// The shape of a launch that is not tuned (kind 0: FP64, 1: FP32).
+// FP32 takes the LDS-tile form, columns looped over only past one workgroup per CU.  Solves of 16 x 8^3
+// with 12 columns (16 bricks) take 14.6 ms with 12 columns per workgroup, 9.4 with 6 and 5.1 with 1; 16 x 16^3 with 3
+// (128 bricks) 8.8 with 3, 8.4 with 2 and 9.7 with 1; the sweep of one slice per chunk 6.0 and 9.7.
+// FP64 does so only where a whole workgroup per CU has columns to loop over (12 columns: 16 x 32^3, 1024
+// bricks, 418 us against the sweep's 579; 32 x 16^3, 256 bricks, 86 against 140; 8 x 16^3, 64 bricks, 36
+// against 31).  Below that the sweep of one slice per chunk, one column per thread: the most workgroups and
+// the shortest serial chain (one column on 32 x 16^3, chunks of 1 and 4 slices: 17.7 and 36 us),
+// with bricks, a brick's slices adjacent and contiguous work per XCD, which the L2 caches need (solves:
+// 16 x 16^3 with 3 columns 12.5 ms against 15.8 in hardware order, 20 x 10^3 with 6 columns 8.0 and 9.8, one
+// column on 32 x 16^3 10.9 and 11.2).
+StencilSched eo_default_sched(const Geo& g, int kind, int ncol) {
+    const bool wide = ncol >= 4 && eo_tile_blocks(eo_tile_shape(g.L, g.nt)) >= 256;
+    if (kind == 1 || wide) {
+        const int kc = eo_tile_cols(g, ncol);
+        return eo_tile_sched(ncol, (ncol + kc - 1) / kc);
+    }
     StencilSched sc;
     sc.nt = kEoNT;
     sc.tc = 1;
+    sc.remap = 1;
+    sc.blocked = 3;
     return sc;
 }
 
@@ -418,8 +436,8 @@ struct EOSystem : System {
 // 4, 8 slices, workgroups in hardware order or XCD-contiguous ranges, 1 or 2
 // columns per thread where allowed, row or brick tiles, tiles or chunks
 // adjacent, plain or non-temporal output stores with two columns; the LDS-tile form with the
-// columns in 1 to 3 groups), cached in the context like the stencil shapes; small fields take
-// eo_default_sched, untimed.
+// columns in 1 to 3 groups and in as many as leave a workgroup per CU), cached in the context like
+// the stencil shapes; small fields take eo_default_sched, untimed.
 template <typename R>
 StencilSched eo_tune(dd_ctx* c, EOSystem& S, const cpx<R>* UR, const cpx<R>* UR12, cpx<R>* tmp, const cpx<R>* in,
                      cpx<R>* out) {
@@ -429,30 +447,46 @@ StencilSched eo_tune(dd_ctx* c, EOSystem& S, const cpx<R>* UR, const cpx<R>* UR1
                             std::to_string(g.whole);
     const auto hit = c->sched.find(key);
     if (hit != c->sched.end()) return hit->second;
-    StencilSched best = eo_default_sched(g, S.ncol);
+    StencilSched best = eo_default_sched(g, sizeof(R) == 8 ? 0 : 1, S.ncol);
     if ((size_t)g.nsite * S.ncol >= ((size_t)1 << 18)) {
         hipEvent_t a, b;
         if (hipEventCreate(&a) == hipSuccess && hipEventCreate(&b) == hipSuccess) {
             const int saved = c->timing;
             c->timing = 0;
             float best_ms = 1e30f;
-            // the best of three timings of three Schur applications (one timing picked shapes by noise)
+            // after a first application, the best of three timings of three (one timing picked shapes by
+            // noise); a shape whose first timing is far behind is not timed again
             auto time_shape = [&](const StencilSched& sc) {
-                for (int w = 0; w < 2; w++)
-                    S.schur<R>(UR, UR12, tmp, sc, 0, EPI_STORE, in, out, nullptr, nullptr, nullptr);
-                float ms = 1e30f;
-                for (int rep = 0; rep < 3; rep++) {
+                auto time = [&](int n) {
                     (void)hipEventRecord(a, c->stream);
-                    for (int r = 0; r < 3; r++)
+                    for (int r = 0; r < n; r++)
                         S.schur<R>(UR, UR12, tmp, sc, 0, EPI_STORE, in, out, nullptr, nullptr, nullptr);
                     (void)hipEventRecord(b, c->stream);
                     (void)hipEventSynchronize(b);
                     float t = 0;
                     (void)hipEventElapsedTime(&t, a, b);
+                    return t;
+                };
+                (void)time(1);
+                float ms = 1e30f;
+                for (int rep = 0; rep < 3; rep++) {
+                    const float t = time(3);
                     ms = t < ms ? t : ms;
+                    if (ms > 1.3f * best_ms) break;
                 }
                 return ms;
             };
+            // the LDS-tile form: columns per workgroup
+            const int kfill = eo_tile_cols(g, S.ncol);
+            for (int parts : {1, 2, 3, (S.ncol + kfill - 1) / kfill}) {
+                if (parts > S.ncol) continue;
+                StencilSched sc = eo_tile_sched(S.ncol, parts);
+                const float ms = time_shape(sc);
+                if (ms < best_ms) {
+                    best_ms = ms;
+                    best = sc;
+                }
+            }
             for (int t : {1, 2, 4, 8})
                 for (int rm = 0; rm < 2; rm++)
                     for (int kc : {1, 2})
@@ -472,16 +506,6 @@ StencilSched eo_tune(dd_ctx* c, EOSystem& S, const cpx<R>* UR, const cpx<R>* UR1
                                 best = sc;
                             }
                         }
-            // the LDS-tile form: columns per workgroup
-            for (int parts : {1, 2, 3}) {
-                if (parts > S.ncol) continue;
-                StencilSched sc = eo_tile_sched(S.ncol, parts);
-                const float ms = time_shape(sc);
-                if (ms < best_ms) {
-                    best_ms = ms;
-                    best = sc;
-                }
-            }
             c->timing = saved;
             (void)hipEventDestroy(a);
             (void)hipEventDestroy(b);
@@ -534,7 +558,7 @@ void launch_eo_merge(dd_ctx* c, const Geo& g, int ncol, const cpx<double>* ev, c
 }
 void launch_eo_hop64(dd_ctx* c, const Geo& g, const cpx<double>* Ueo, double a_self, double c_hop, int p_out, int dag,
                      const cpx<double>* in, const cpx<double>* self, cpx<double>* out, int ncol) {
-    const StencilSched sc = eo_default_sched(g, ncol);
+    const StencilSched sc = eo_default_sched(g, 0, ncol);
     launch_eo_hop<double>(c, g, Ueo, nullptr, a_self, c_hop, p_out, dag, EPI_STORE, in, self, out, nullptr, ncol, sc.tc,
                           sc.kc, sc.remap, sc.blocked, nullptr, nullptr);
 }
