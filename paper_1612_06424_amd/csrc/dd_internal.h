@@ -105,7 +105,6 @@ struct ColState {
     int active;                 // 1 while iterating
     int iters;                  // iterations done by this column
     int breakdown;              // 1: stalled (rho, <r^,v> or omega vanished), 2: non-finite
-    int xdue;                   // CGNR: alpha p of the current iteration still to be added to x
 };
 
 // ------------------------------------------------------------------ context
@@ -177,7 +176,7 @@ enum Slot {
     W_R = 0, W_RH, W_P, W_V, W_S, W_T,          // Krylov vectors, FP64
     W_R32, W_RH32, W_P32, W_V32, W_S32, W_T32,  // Krylov vectors, FP32
     W_B32, W_X32, W_U32, W_RES64,
-    W_PART, W_STATE, W_STATE32, W_DOTS,
+    W_PART, W_PART_CG, W_STATE, W_STATE32, W_DOTS,
     W_AUX0, W_AUX1, W_AUX2, W_AUX3, W_AUX4,
     W_SEGS, W_SEGN, W_EO_B, W_EO_X, W_EO_BHAT, W_EO_T64, W_EO_T32, W_EO_U64, W_BATCH0, W_BATCH1, W_BATCH2, W_BATCH3, W_BATCH4,
     W_U32C, W_LDEV, W_PROJ_V, W_PROJ_G, W_PROJ_R, W_DISC0, W_DISC1, W_DISC2, W_DISC3,
@@ -255,6 +254,13 @@ struct Segs {
     int paired;            // FP32 vectors are even-odd half fields with paired components (dd_eo.h)
 };
 
+// One sum per segment out of partial slots of three doubles, of which the first counts: slots
+// [p0[seg], p0[seg + 1]), or slot seg where p0 is null.
+struct SlotSum {
+    const int* p0;
+    const double* part;
+};
+
 // Vector kernels of the Krylov solvers over segments; reductions write one
 // partial slot per elementwise workgroup (slots of segment k: [eb0[k], eb0[k+1])).
 template <typename R>
@@ -265,9 +271,11 @@ template <typename R>
 void launch_bicg_xr(dd_ctx* c, const Segs& S, cpx<R>* x, cpx<R>* r, const cpx<R>* p, const cpx<R>* s,
                     const cpx<R>* t, const cpx<R>* rh, double* partial, const ColState* st);
 template <typename R>
-void launch_cg_r(dd_ctx* c, const Segs& S, cpx<R>* r, const cpx<R>* w, double* partial, const ColState* st);
+void launch_cg_r(dd_ctx* c, const Segs& S, cpx<R>* r, const cpx<R>* w, SlotSum ww, double* partial,
+                 const ColState* st, ColState* st_out);
 template <typename R>
-void launch_cg_px(dd_ctx* c, const Segs& S, cpx<R>* x, cpx<R>* p, const cpx<R>* z, const ColState* st);
+void launch_cg_px(dd_ctx* c, const Segs& S, cpx<R>* x, cpx<R>* p, const cpx<R>* z, SlotSum rr, SlotSum zz,
+                  const ColState* st, ColState* st_out);
 template <typename R>
 void launch_norm2(dd_ctx* c, const Segs& S, const cpx<R>* a, double* partial);
 template <typename R>
@@ -290,12 +298,13 @@ enum Fin {
     FIN_ALPHA = 0,   // dots = <r^,v>        -> alpha = rho / <r^,v>
     FIN_OMEGA,       // dots = <t,s>, |t|^2  -> omega
     FIN_RHO,         // dots = <r^,r>, |r|^2 -> beta, rho, rr, convergence
-    FIN_CG_ALPHA,    // dots = |w|^2         -> alpha = zz / |w|^2
-    FIN_CG_RR,       // dots = |r|^2         -> rr, convergence
-    FIN_CG_BETA,     // dots = |z|^2         -> beta = zz_new / zz
     FIN_CG_ZZ,       // dots = |z|^2         -> zz
     FIN_STORE        // dots -> out[seg*3 + k] (plain reduction)
 };
+// out[seg] (three doubles, the first used) = the segment's sum, for one or two sums (b.part null: one;
+// the second's results follow at out + 3 nseg).
+void launch_presum(dd_ctx* c, int nseg, SlotSum a, SlotSum b, double* out);
+
 // p0: device [nseg + 1] prefix of the partial slots of each segment.
 void launch_finalize(dd_ctx* c, int fin, int nseg, const int* p0, const double* partial, ColState* st,
                      double* out);
@@ -311,6 +320,8 @@ struct System {
     Segs seg{};                            // elementwise segment tables
     const int* sp0[2] = {nullptr, nullptr};
     size_t nslots = 0;                     // partial slots needed by any launch
+    int seg_slots[2] = {0, 0};             // most stencil slots of a segment, per kind
+    int seg_eb = 0;                        // most elementwise workgroups of a segment
     bool graph = false;                    // replay the inner iterations from a captured HIP graph
     bool has32 = false;                    // FP32 stencil available (links converted)
     bool pair32 = false;                   // FP32 vectors are half fields with paired components

@@ -158,19 +158,74 @@ __global__ __launch_bounds__(kBlock) void k_bicg_xr(Segs S, cpx<R>* __restrict__
     block_sum3(d0, d1, d2, partial + (size_t)blockIdx.x * 3);
 }
 
-// CGNR: r -= alpha w; partial |r|^2 (alpha real)
+// A thread's share of a segment's sum, and the workgroup's totals of two shares, in every thread:
+// the order of k_finalize.
+__device__ inline double slot_share(const SlotSum& s, int seg) {
+    double d = 0;
+    const int k0 = s.p0 ? s.p0[seg] : seg, k1 = s.p0 ? s.p0[seg + 1] : seg + 1;
+    for (int k = k0 + (int)threadIdx.x; k < k1; k += kBlock) d += s.part[3 * (size_t)k];
+    return d;
+}
+__device__ inline void block_total2(double& a, double& b) {
+    __shared__ double sh[kBlock / kWave][2];
+    a = wave_sum(a);
+    b = wave_sum(b);
+    if (threadIdx.x % kWave == 0) {
+        sh[threadIdx.x / kWave][0] = a;
+        sh[threadIdx.x / kWave][1] = b;
+    }
+    __syncthreads();
+    a = b = 0;
+#pragma unroll
+    for (int k = 0; k < kBlock / kWave; k++) {
+        a += sh[k][0];
+        b += sh[k][1];
+    }
+}
+
+// The scalar recurrences of CGNR have no kernels of their own: the two vector kernels of an
+// iteration add up the partial slots of the applications before them, every workgroup those of its
+// segment, while its vector loads are in flight.  (A k_finalize launch for each of the three sums took
+// 3 to 5 us and left a gap after it: 12 of 55 us of an iteration on 8 x 4^3, 13 of 75 on 32 x 16^3.)
+// Each reads one copy of the segment's state and the segment's first workgroup writes the
+// other copy, so no workgroup reads what another one of the launch writes.
+
+// r -= alpha w with alpha = zz / |w|^2; partial |r|^2.  A vanishing or non-finite |w|^2 stops the column.
 template <typename R>
 __global__ __launch_bounds__(kBlock) void k_cg_r(Segs S, cpx<R>* __restrict__ r_, const cpx<R>* __restrict__ w_,
-                                                 double* __restrict__ partial, const ColState* __restrict__ st) {
+                                                 SlotSum ww, double* __restrict__ partial,
+                                                 const ColState* __restrict__ st, ColState* __restrict__ st_out) {
     LANE_SETUP(R);
-    if (!st[q.seg].active) return;
-    double d0 = 0;
-    const R a = R(st[q.seg].alpha_re);
+    const ColState& s = st[q.seg];
+    const bool writer = (int)blockIdx.x == S.eb0[q.seg] && threadIdx.x == 0;
+    if (!s.active) {  // uniform over the workgroup
+        if (writer) st_out[q.seg] = s;
+        return;
+    }
     T* r = AS(T, r_);
     const T* w = AS_C(T, w_);
     T rv[NE], wv[NE];
-    SEG_LOOP((rv[j] = r[q.at(j)], wv[j] = w[q.at(j)]),
-             ({
+    SEG_LOOP((rv[j] = r[q.at(j)], wv[j] = w[q.at(j)]), (void)0)
+    double den = slot_share(ww, q.seg), none = 0;
+    block_total2(den, none);
+    const bool ok = den > 0 && isfinite(den);
+    const double alpha = s.zz / den;
+    if (writer) {
+        ColState t = s;
+        t.alpha_re = alpha;
+        t.alpha_im = 0;
+        if (!ok) {
+            t.alpha_re = s.alpha_re;
+            t.alpha_im = s.alpha_im;
+            t.breakdown = isfinite(den) ? 1 : 2;
+            t.active = 0;
+        }
+        st_out[q.seg] = t;
+    }
+    if (!ok) return;
+    double d0 = 0;
+    const R a = R(alpha);
+    SEG_LOOP((void)0, ({
                  const T rn = rv[j] - a * wv[j];
                  r[q.at(j)] = rn;
                  norm_acc(d0, rn);
@@ -178,27 +233,44 @@ __global__ __launch_bounds__(kBlock) void k_cg_r(Segs S, cpx<R>* __restrict__ r_
     block_sum3(d0, 0.0, 0.0, partial + (size_t)blockIdx.x * 3);
 }
 
-// CGNR, the end of an iteration: x += alpha p while that update is due (also for a
-// column that stopped in this iteration), then p = z + beta p for running columns
-// (alpha, beta real).  The x update waits until here so that p is read once.
+// The end of an iteration: x += alpha p, p = z + beta p with beta = |z|^2 / zz (p is read once for both), the
+// new |r|^2 and the stopping test.  A column that stops here has taken its last step in full, z and p
+// included, and could go on from it.
 template <typename R>
 __global__ __launch_bounds__(kBlock) void k_cg_px(Segs S, cpx<R>* __restrict__ x_, cpx<R>* __restrict__ p_,
-                                                  const cpx<R>* __restrict__ z_, const ColState* __restrict__ st) {
+                                                  const cpx<R>* __restrict__ z_, SlotSum rr, SlotSum zz,
+                                                  const ColState* __restrict__ st, ColState* __restrict__ st_out) {
     LANE_SETUP(R);
     const ColState& s = st[q.seg];
-    const bool run = s.active != 0, due = s.xdue != 0;  // uniform over the workgroup
-    if (!run && !due) return;
-    const R a = R(s.alpha_re), b = R(s.beta_re);
+    const bool writer = (int)blockIdx.x == S.eb0[q.seg] && threadIdx.x == 0;
+    if (!s.active) {  // uniform over the workgroup
+        if (writer) st_out[q.seg] = s;
+        return;
+    }
     T* x = AS(T, x_);
     T* p = AS(T, p_);
     const T* z = AS_C(T, z_);
     T xv[NE], pv[NE], zv[NE];
-    if (run) {
-        SEG_LOOP((xv[j] = x[q.at(j)], pv[j] = p[q.at(j)], zv[j] = z[q.at(j)]),
-                 (x[q.at(j)] = xv[j] + a * pv[j], p[q.at(j)] = zv[j] + b * pv[j]))
-    } else {
-        SEG_LOOP((xv[j] = x[q.at(j)], pv[j] = p[q.at(j)]), (x[q.at(j)] = xv[j] + a * pv[j]))
+    SEG_LOOP((xv[j] = x[q.at(j)], pv[j] = p[q.at(j)], zv[j] = z[q.at(j)]), (void)0)
+    double r2 = slot_share(rr, q.seg), z2 = slot_share(zz, q.seg);
+    block_total2(r2, z2);
+    const double beta = z2 / s.zz;
+    const R a = R(s.alpha_re), b = R(beta);
+    SEG_LOOP((void)0, (x[q.at(j)] = xv[j] + a * pv[j], p[q.at(j)] = zv[j] + b * pv[j]))
+    if (!writer) return;
+    ColState t = s;
+    t.rr = r2;
+    t.iters += 1;
+    t.beta_re = beta;
+    t.beta_im = 0;
+    t.zz = z2;
+    if (!isfinite(r2)) {
+        t.breakdown = 2;
+        t.active = 0;
+    } else if (r2 <= s.stop2) {
+        t.active = 0;
     }
+    st_out[q.seg] = t;
 }
 
 // partial |a|^2 of every segment
@@ -300,11 +372,7 @@ __global__ __launch_bounds__(kBlock) void k_finalize(int fin, const int* __restr
                                                      const double* __restrict__ partial, ColState* __restrict__ st,
                                                      double* __restrict__ out) {
     const int seg = blockIdx.x;
-    if (fin != FIN_STORE && !st[seg].active) {
-        // a stopped column: its last x update (if any) was applied by k_cg_px
-        if (fin == FIN_CG_ALPHA && threadIdx.x == 0) st[seg].xdue = 0;
-        return;
-    }
+    if (fin != FIN_STORE && !st[seg].active) return;
     double d0 = 0, d1 = 0, d2 = 0;
     const int k0 = p0[seg], k1 = p0[seg + 1];
     for (int k = k0 + (int)threadIdx.x; k < k1; k += kBlock) {
@@ -381,35 +449,6 @@ __global__ __launch_bounds__(kBlock) void k_finalize(int fin, const int* __restr
             }
             break;
         }
-        case FIN_CG_ALPHA: {
-            s.xdue = 0;  // the previous iteration's update was applied; due again once alpha is known
-            if (!(d0 > 0) || !isfinite(d0)) {
-                s.breakdown = isfinite(d0) ? 1 : 2;
-                s.active = 0;
-                break;
-            }
-            s.alpha_re = s.zz / d0;
-            s.alpha_im = 0;
-            s.xdue = 1;
-            break;
-        }
-        case FIN_CG_RR: {
-            s.rr = d0;
-            s.iters += 1;
-            if (!isfinite(d0)) {
-                s.breakdown = 2;
-                s.active = 0;
-            } else if (d0 <= s.stop2) {
-                s.active = 0;
-            }
-            break;
-        }
-        case FIN_CG_BETA: {
-            s.beta_re = d0 / s.zz;
-            s.beta_im = 0;
-            s.zz = d0;
-            break;
-        }
         case FIN_CG_ZZ: {
             s.zz = d0;
             if (!(d0 > 0) || !isfinite(d0)) {
@@ -423,6 +462,12 @@ __global__ __launch_bounds__(kBlock) void k_finalize(int fin, const int* __restr
     }
 }
 
+// One workgroup per segment and sum: the segment's slots, added in k_finalize's order, as one slot.
+__global__ __launch_bounds__(kBlock) void k_presum(SlotSum a, SlotSum b, double* __restrict__ out) {
+    double d = slot_share(blockIdx.y ? b : a, (int)blockIdx.x), none = 0;
+    block_total2(d, none);
+    if (threadIdx.x == 0) out[3 * ((size_t)blockIdx.y * gridDim.x + blockIdx.x)] = d;
+}
 
 #undef SEG_LOOP
 #undef LANE_SETUP
@@ -447,12 +492,17 @@ void launch_bicg_xr(dd_ctx* c, const Segs& S, cpx<R>* x, cpx<R>* r, const cpx<R>
     hipLaunchKernelGGL(k_bicg_xr<R>, sgrid(S), dim3(kBlock), 0, c->stream, S, x, r, p, s, t, rh, partial, st);
 }
 template <typename R>
-void launch_cg_r(dd_ctx* c, const Segs& S, cpx<R>* r, const cpx<R>* w, double* partial, const ColState* st) {
-    hipLaunchKernelGGL(k_cg_r<R>, sgrid(S), dim3(kBlock), 0, c->stream, S, r, w, partial, st);
+void launch_cg_r(dd_ctx* c, const Segs& S, cpx<R>* r, const cpx<R>* w, SlotSum ww, double* partial,
+                 const ColState* st, ColState* st_out) {
+    hipLaunchKernelGGL(k_cg_r<R>, sgrid(S), dim3(kBlock), 0, c->stream, S, r, w, ww, partial, st, st_out);
 }
 template <typename R>
-void launch_cg_px(dd_ctx* c, const Segs& S, cpx<R>* x, cpx<R>* p, const cpx<R>* z, const ColState* st) {
-    hipLaunchKernelGGL(k_cg_px<R>, sgrid(S), dim3(kBlock), 0, c->stream, S, x, p, z, st);
+void launch_cg_px(dd_ctx* c, const Segs& S, cpx<R>* x, cpx<R>* p, const cpx<R>* z, SlotSum rr, SlotSum zz,
+                  const ColState* st, ColState* st_out) {
+    hipLaunchKernelGGL(k_cg_px<R>, sgrid(S), dim3(kBlock), 0, c->stream, S, x, p, z, rr, zz, st, st_out);
+}
+void launch_presum(dd_ctx* c, int nseg, SlotSum a, SlotSum b, double* out) {
+    hipLaunchKernelGGL(k_presum, dim3((unsigned)nseg, b.part ? 2u : 1u), dim3(kBlock), 0, c->stream, a, b, out);
 }
 template <typename R>
 void launch_norm2(dd_ctx* c, const Segs& S, const cpx<R>* a, double* partial) {
@@ -493,8 +543,10 @@ void launch_finalize(dd_ctx* c, int fin, int nseg, const int* p0, const double* 
     template void launch_bicg_s<R>(dd_ctx*, const Segs&, const cpx<R>*, const cpx<R>*, cpx<R>*, const ColState*); \
     template void launch_bicg_xr<R>(dd_ctx*, const Segs&, cpx<R>*, cpx<R>*, const cpx<R>*, const cpx<R>*,       \
                                     const cpx<R>*, const cpx<R>*, double*, const ColState*);                   \
-    template void launch_cg_r<R>(dd_ctx*, const Segs&, cpx<R>*, const cpx<R>*, double*, const ColState*);       \
-    template void launch_cg_px<R>(dd_ctx*, const Segs&, cpx<R>*, cpx<R>*, const cpx<R>*, const ColState*);     \
+    template void launch_cg_r<R>(dd_ctx*, const Segs&, cpx<R>*, const cpx<R>*, SlotSum, double*, const ColState*, \
+                                 ColState*);                                                                    \
+    template void launch_cg_px<R>(dd_ctx*, const Segs&, cpx<R>*, cpx<R>*, const cpx<R>*, SlotSum, SlotSum,      \
+                                  const ColState*, ColState*);                                                   \
     template void launch_norm2<R>(dd_ctx*, const Segs&, const cpx<R>*, double*);                               \
     template void launch_copy_segs<R>(dd_ctx*, const Segs&, const cpx<R>*, cpx<R>*, const ColState*);          \
     template void launch_fold_x<R>(dd_ctx*, const Segs&, cpx<double>*, cpx<R>*, const int*);                   \

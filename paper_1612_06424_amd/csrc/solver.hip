@@ -157,6 +157,7 @@ class InnerRounds {
 struct Work {
     ColState* st;
     double* partial;
+    double* partial_cg;  // CGNR: slots of |r|^2, then six doubles per segment for sums taken ahead
     double* dots;
     int* mask_dev;
     cpx<double>* r64;
@@ -322,6 +323,13 @@ dd_status bicgstab_reliable(System& S, const cpx<double>* b, cpx<double>* x, con
     return DD_OK;
 }
 
+// Most partial slots of a segment that every workgroup of a CGNR vector kernel adds up itself; longer
+// rows are added up once, by a launch of their own.  Solves of 2 columns, own launch and inline, ms: 64 x
+// 32^3 mixed (6144 slots) 136.4 and 140.0, 32 x 32^3 FP64 (3072) 143.6 and 146.4; 4 columns of 16 x 32^3 mixed
+// (1536) 49.5 and 49.6; 12 columns of 8 x 16^3 mixed (96) 24 vectors 19.2 and 18.6, force on 32 x 16^3 (384) 20.6
+// and 19.7.
+constexpr int kMaxInlineSlots = 1024;
+
 // CGNR (CG on D^+ D x = D^+ b) with reliable updates: when a segment's residual
 // has dropped by delta, or the recursion stopped, the host folds the correction
 // into the FP64 solution, recomputes the true FP64 residual r = b - D x,
@@ -383,14 +391,19 @@ dd_status cgnr_reliable(System& S, const cpx<double>* b, cpx<double>* x, const s
         launch_copy_segs<R>(c, S.seg, z, pp, st);
     }
     InnerRounds rounds(S, check_every);
+    // The state after the first half of an iteration; between iterations it is in st.
+    ColState* st2 = st + ns;
+    const SlotSum hop{S.sp0[kind], partial}, res2{S.seg.eb0, W.partial_cg};
+    double* sums = W.partial_cg + 3 * (size_t)S.seg.neb;
+    const bool presum = std::max(S.seg_slots[kind], S.seg_eb) > kMaxInlineSlots;
     auto iteration = [&]() {
         S.apply(0, EPI_NORM, pp, wv, (const cpx<R>*)nullptr, partial, st);
-        launch_finalize(c, FIN_CG_ALPHA, ns, S.sp0[kind], partial, st, nullptr);
-        launch_cg_r<R>(c, S.seg, r, wv, partial, st);
-        launch_finalize(c, FIN_CG_RR, ns, S.seg.eb0, partial, st, nullptr);
-        S.apply(1, EPI_NORM, r, z, (const cpx<R>*)nullptr, partial, st);
-        launch_finalize(c, FIN_CG_BETA, ns, S.sp0[kind], partial, st, nullptr);
-        launch_cg_px<R>(c, S.seg, xx, pp, z, st);  // x += alpha p (also as a column stops), p = z + beta p
+        if (presum) launch_presum(c, ns, hop, SlotSum{nullptr, nullptr}, sums);
+        launch_cg_r<R>(c, S.seg, r, wv, presum ? SlotSum{nullptr, sums} : hop, W.partial_cg, st, st2);
+        S.apply(1, EPI_NORM, r, z, (const cpx<R>*)nullptr, partial, st2);
+        if (presum) launch_presum(c, ns, res2, hop, sums);
+        launch_cg_px<R>(c, S.seg, xx, pp, z, presum ? SlotSum{nullptr, sums} : res2,
+                        presum ? SlotSum{nullptr, sums + 3 * (size_t)ns} : hop, st2, st);
     };
     while (ndone < ns && total < p.max_iter) {
         const int k = std::min(check_every, p.max_iter - total);
@@ -530,6 +543,12 @@ dd_status SegLayout::upload(dd_ctx* c, Slot slot, System* S) {
     S->nslots = std::max(S->nslots, (size_t)neb);
     S->nslots = std::max(S->nslots, (size_t)sp0[0][ns]);
     S->nslots = std::max(S->nslots, (size_t)sp0[1][ns]);
+    S->seg_slots[0] = S->seg_slots[1] = S->seg_eb = 0;
+    for (int k = 0; k < ns; k++) {
+        for (int kind = 0; kind < 2; kind++)
+            S->seg_slots[kind] = std::max(S->seg_slots[kind], sp0[kind][k + 1] - sp0[kind][k]);
+        S->seg_eb = std::max(S->seg_eb, eb0[k + 1] - eb0[k]);
+    }
     return DD_OK;
 }
 
@@ -542,7 +561,9 @@ dd_status solve_system(System& S, const cpx<double>* b, cpx<double>* x, const dd
     Work W{};
     W.partial = (double*)workspace(c, W_PART, S.nslots * 3 * sizeof(double), &e);
     if (e != DD_OK) return e;
-    W.st = (ColState*)workspace(c, W_STATE, sizeof(ColState) * ns, &e);
+    W.partial_cg = (double*)workspace(c, W_PART_CG, ((size_t)S.seg.neb * 3 + (size_t)ns * 6) * sizeof(double), &e);
+    if (e != DD_OK) return e;
+    W.st = (ColState*)workspace(c, W_STATE, 2 * sizeof(ColState) * ns, &e);
     if (e != DD_OK) return e;
     W.dots = (double*)workspace(c, W_DOTS, sizeof(double) * 3 * ns, &e);
     if (e != DD_OK) return e;
