@@ -22,8 +22,8 @@
 // P = N_m (N_m + 1) / 2 pairs i <= j only: B is symmetric in (i, j) (C gamma5 and
 // eps are both antisymmetric).  The diquarks E (HBM-bound) and the packed quark
 // matrix are written per chunk; the product is a complex FP64 GEMM on the matrix
-// cores (k_zgemm_mfma: 64 x 64 tiles of four 16 x 16 x 4 FP64 MFMA blocks per
-// wavefront, operands staged through LDS, the k range split so that the grid
+// cores (k_zgemm_mfma: tiles of 64 x 32, 64 or 96 in 16 x 16 x 4 FP64 MFMA
+// blocks, operands staged through LDS, the k range split so that the grid
 // fills the chip, the splits added in a fixed order by k_zgemm_reduce)
 // accumulating into the slice's packed blocks, and a last kernel writes both
 // (i, j) and (j, i).  About N_m / 2 flops per byte of E, so the product, not the
@@ -126,26 +126,68 @@ __global__ __launch_bounds__(kNB) void k_diquarks(int n, long long nsite, long l
 // (lane l holds A[l % 16][l / 16]) by a 4 x 16 block (lane l holds B[l / 16][l % 16])
 // into a 16 x 16 accumulator (lane l holds rows l / 16 + 4 e, e = 0..3, of column l % 16).
 // A complex product is four real ones: re += ar br + ai (-bi), im += ar bi + ai br.
-// A workgroup (four wavefronts, 2 x 2) owns a 64 x 64 tile of C and one of nsplit
-// ranges of k (kps steps of 16); per step the 64 x 16 panel of A and the 16 x 64
+// A workgroup (four wavefronts, 2 x 2) owns a 64 x 32 NJ tile of C and one of nsplit
+// ranges of k (kps steps of 16); per step the 64 x 16 panel of A and the 16 x 32 NJ
 // panel of B go through LDS (the next step's panels are loaded into registers while
-// the current one is multiplied), and each wavefront runs 16 MFMAs per 4 values of
-// k on its 32 x 32 quarter (132 registers: three wavefronts per SIMD; a form holding
-// the step's operands up front took 212 and ran 16 % slower).  Each split writes its own partial C; k_zgemm_reduce
+// the current one is multiplied), and each wavefront runs 8 NJ MFMAs per 4 values of
+// k on its 32 x 16 NJ quarter (NJ = 3: 184 registers, two wavefronts per SIMD; NJ = 2: 132
+// registers, three; a form of that holding the step's operands up front took 212 and ran 16 %
+// slower).  What bounds it: the matrix cores, busy 97 % of the time at the clock that the card holds;
+// tiles 64 wide spent 6 % of it on padding 480 columns (120 vectors) to 512: per 6162 sites 7.25
+// ms, 96 wide 6.93.  Each split writes its own partial C; k_zgemm_reduce
 // adds them in a fixed order, so the result does not depend on scheduling.
 typedef double dbl4 __attribute__((ext_vector_type(4)));
 typedef double dbl2 __attribute__((ext_vector_type(2)));
-constexpr int kGM = 64, kGN = 64, kGK = 16;  // workgroup tile (complex entries) and k step
+constexpr int kGM = 64, kGK = 16;  // rows of a workgroup's tile (complex entries) and k step
 constexpr int kGThreads = 256;
 
 __device__ __forceinline__ dbl2 gload2(rsrc_t r, uint32_t voff) {
     return __builtin_bit_cast(dbl2, __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, 0, 0));
 }
 
+// Blocks of 16 columns per wavefront (tile width 32 nj): the width that pads N least, one block only if it
+// saves more than a tenth (its LDS reads per MFMA are twice those of three: 100 vectors, 416 columns of it 3.92 ms,
+// 448 of two 3.88), and the wider of two that pad alike.  120 vectors: 480 columns of three, 512 of two.
+int zgemm_blocks(int N) {
+    const auto cost = [&](int nj) { return (N + 32 * nj - 1) / (32 * nj) * nj * (nj == 1 ? 1.1 : 1.0); };
+    int best = 1;
+    for (int nj = 2; nj <= 3; nj++)
+        if (cost(nj) <= cost(best)) best = nj;
+    return best;
+}
+
+// Splits of the k range for ntile tiles of nj blocks, nkt steps of k and MN entries: the least of the estimated
+// times of the product and of writing and adding the partial results, with at most about 16 workgroups per CU
+// in all.  A step of a wavefront is 32 nj MFMAs of 64 cycles; w workgroups on a CU share its matrix cores, and a
+// step has 1.1 us of latency that only the others hide; `fit` workgroups run per CU, the last round with as
+// many as are left, and a tenth of a round is lost to uneven ends.  Blocks on one 16^3
+// slice, 16 workgroups per CU throughout and so, ms: 4 vectors 0.23 and 0.075, 24 0.27 and 0.15, 48 0.61
+// and 0.54, 80 1.92 and 1.87.
+int zgemm_splits(int ntile, int nj, int nkt, size_t MN) {
+    const int fit = nj == 3 ? 2 : nj == 2 ? 3 : 5, lim = std::max(1, std::min(nkt, (16 * 256 + ntile - 1) / ntile));
+    const double mfma = 2048.0 * nj / 2.35e3;  // us of a step per workgroup on the CU
+    const auto step = [&](long long w) { return w ? std::max((double)w * mfma, mfma + 1.1) : 0.0; };
+    int best = 1;
+    double best_us = 1e30;
+    for (int ns = 1; ns <= lim; ns++) {
+        const int kps = (nkt + ns - 1) / ns;
+        const long long wgs = (long long)ntile * ns, full = wgs / (256 * fit), rem = wgs % (256 * fit);
+        const double us = kps * ((double)full * step(fit) + step((rem + 255) / 256) + 0.1 * step(fit)) +
+                          ns * (0.15 + (double)MN * 2 * sizeof(cpx<double>) / 5e6);
+        if (us < best_us) {
+            best_us = us;
+            best = ns;
+        }
+    }
+    return best;
+}
+
+template <int NJ>
 __global__ __launch_bounds__(kGThreads, 2) void k_zgemm_mfma(int M, int N, int K, int kps,
                                                              const cpx<double>* __restrict__ A,
                                                              const cpx<double>* __restrict__ B,
                                                              cpx<double>* __restrict__ Cpart) {
+    constexpr int kGN = 32 * NJ;
     __shared__ dbl2 As[kGK][kGM + 1];  // As[k][m]; one entry of padding per row
     __shared__ dbl2 Bs[kGK][kGN + 1];  // Bs[k][n]
     const int tm = (M + kGM - 1) / kGM, tn = (N + kGN - 1) / kGN;
@@ -163,7 +205,7 @@ __global__ __launch_bounds__(kGThreads, 2) void k_zgemm_mfma(int M, int N, int K
     // global -> LDS roles: A entries (m = tid % 64, k = tid / 64 + 4 r), B entries (k = tid % 16, n = tid / 16 + 16 r)
     const int am = tid & 63, ak = tid >> 6;
     const int bk = tid & 15, bn = tid >> 4;
-    dbl2 ga[4], gb[4];
+    dbl2 ga[4], gb[2 * NJ];
     auto fetch = [&](int kt) {
         const int k0 = kt * kGK;
 #pragma unroll
@@ -174,7 +216,7 @@ __global__ __launch_bounds__(kGThreads, 2) void k_zgemm_mfma(int M, int N, int K
             ga[r] = ok ? v : dbl2{0.0, 0.0};
         }
 #pragma unroll
-        for (int r = 0; r < 4; r++) {
+        for (int r = 0; r < 2 * NJ; r++) {
             const int k = k0 + bk, n = n0 + bn + 16 * r;
             const bool ok = k < K && n < N;
             const dbl2 v = gload2(rb, ok ? (uint32_t)(((size_t)n * K + k) * sizeof(cpx<double>)) : 0u);
@@ -185,14 +227,14 @@ __global__ __launch_bounds__(kGThreads, 2) void k_zgemm_mfma(int M, int N, int K
 #pragma unroll
         for (int r = 0; r < 4; r++) As[ak + 4 * r][am] = ga[r];
 #pragma unroll
-        for (int r = 0; r < 4; r++) Bs[bk][bn + 16 * r] = gb[r];
+        for (int r = 0; r < 2 * NJ; r++) Bs[bk][bn + 16 * r] = gb[r];
     };
 
-    dbl4 cr[2][2], ci[2][2];
+    dbl4 cr[2][NJ], ci[2][NJ];
 #pragma unroll
     for (int i = 0; i < 2; i++)
 #pragma unroll
-        for (int j = 0; j < 2; j++) cr[i][j] = ci[i][j] = dbl4{0.0, 0.0, 0.0, 0.0};
+        for (int j = 0; j < NJ; j++) cr[i][j] = ci[i][j] = dbl4{0.0, 0.0, 0.0, 0.0};
 
     if (kt0 < kt1) {
         fetch(kt0);
@@ -204,34 +246,37 @@ __global__ __launch_bounds__(kGThreads, 2) void k_zgemm_mfma(int M, int N, int K
 #pragma unroll
         for (int ks = 0; ks < kGK / 4; ks++) {
             const int kk = 4 * ks + (lane >> 4);
-            double ar[2], ai[2], br[2], bi[2], bm[2];
+            double ar[2], ai[2], br[NJ], bi[NJ], bm[NJ];
 #pragma unroll
             for (int i = 0; i < 2; i++) {
                 const dbl2 a = As[kk][wm * 32 + i * 16 + (lane & 15)];
                 ar[i] = a.x;
                 ai[i] = a.y;
-                const dbl2 b = Bs[kk][wn * 32 + i * 16 + (lane & 15)];
-                br[i] = b.x;
-                bi[i] = b.y;
-                bm[i] = -b.y;
+            }
+#pragma unroll
+            for (int j = 0; j < NJ; j++) {
+                const dbl2 b = Bs[kk][wn * 16 * NJ + j * 16 + (lane & 15)];
+                br[j] = b.x;
+                bi[j] = b.y;
+                bm[j] = -b.y;
             }
             // consecutive MFMAs go to different accumulators
 #pragma unroll
             for (int i = 0; i < 2; i++)
 #pragma unroll
-                for (int j = 0; j < 2; j++) cr[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar[i], br[j], cr[i][j], 0, 0, 0);
+                for (int j = 0; j < NJ; j++) cr[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar[i], br[j], cr[i][j], 0, 0, 0);
 #pragma unroll
             for (int i = 0; i < 2; i++)
 #pragma unroll
-                for (int j = 0; j < 2; j++) ci[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar[i], bi[j], ci[i][j], 0, 0, 0);
+                for (int j = 0; j < NJ; j++) ci[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(ar[i], bi[j], ci[i][j], 0, 0, 0);
 #pragma unroll
             for (int i = 0; i < 2; i++)
 #pragma unroll
-                for (int j = 0; j < 2; j++) cr[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(ai[i], bm[j], cr[i][j], 0, 0, 0);
+                for (int j = 0; j < NJ; j++) cr[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(ai[i], bm[j], cr[i][j], 0, 0, 0);
 #pragma unroll
             for (int i = 0; i < 2; i++)
 #pragma unroll
-                for (int j = 0; j < 2; j++) ci[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(ai[i], br[j], ci[i][j], 0, 0, 0);
+                for (int j = 0; j < NJ; j++) ci[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(ai[i], br[j], ci[i][j], 0, 0, 0);
         }
         __syncthreads();  // every wavefront is done with the panels
         if (kt + 1 < kt1) {
@@ -246,11 +291,11 @@ __global__ __launch_bounds__(kGThreads, 2) void k_zgemm_mfma(int M, int N, int K
 #pragma unroll
     for (int i = 0; i < 2; i++)
 #pragma unroll
-        for (int j = 0; j < 2; j++)
+        for (int j = 0; j < NJ; j++)
 #pragma unroll
             for (int e = 0; e < 4; e++) {
                 const int row = m0 + wm * 32 + i * 16 + (lane >> 4) + 4 * e;
-                const int col = n0 + wn * 32 + j * 16 + (lane & 15);
+                const int col = n0 + wn * 16 * NJ + j * 16 + (lane & 15);
                 if (row < M && col < N) {
                     const uint32_t vo = (uint32_t)(((size_t)col * M + row) * sizeof(cpx<double>));
                     // the elements go through scalars: a bit cast of a vector element expression
@@ -449,11 +494,11 @@ dd_status baryon_blocks(dd_ctx* c, int n, int nt, const cpx<double>* s, cpx<doub
     cpx<double>* Bp = E + M * 3 * X;  // the packed blocks of one slice
     cpx<double>* Sp = (cpx<double>*)workspace(c, W_DISC3, (size_t)3 * X * 4 * n * sizeof(cpx<double>), &e);
     if (e != DD_OK) return e;
-    // the k range of a chunk's product is split so that about 16 workgroups per CU run in all
     const int N = 4 * n;
-    const int ntile = (int)(((M + kGM - 1) / kGM) * ((N + kGN - 1) / kGN));
+    const int nj = zgemm_blocks(N);
+    const int ntile = (int)(((M + kGM - 1) / kGM) * ((N + 32 * nj - 1) / (32 * nj)));
     const int nkt_max = (3 * X + kGK - 1) / kGK;
-    const int nsplit_max = std::max(1, std::min(nkt_max, (16 * 256 + ntile - 1) / ntile));
+    const int nsplit_max = zgemm_splits(ntile, nj, nkt_max, M * N);  // of a whole chunk; a last one has no more
     cpx<double>* Cpart =
         (cpx<double>*)workspace(c, W_DISC1, (size_t)nsplit_max * M * N * sizeof(cpx<double>), &e);
     if (e != DD_OK) return e;
@@ -471,8 +516,9 @@ dd_status baryon_blocks(dd_ctx* c, int n, int nt, const cpx<double>* s, cpx<doub
             const int nkt = (K + kGK - 1) / kGK;
             const int kps = (nkt + nsplit_max - 1) / nsplit_max;
             const int nsplit = (nkt + kps - 1) / kps;
-            hipLaunchKernelGGL(k_zgemm_mfma, dim3((unsigned)(ntile * nsplit)), dim3(kGThreads), 0, c->stream, (int)M, N,
-                               K, kps, E, Sp, Cpart);
+            const auto kern = nj == 3 ? k_zgemm_mfma<3> : nj == 2 ? k_zgemm_mfma<2> : k_zgemm_mfma<1>;
+            hipLaunchKernelGGL(kern, dim3((unsigned)(ntile * nsplit)), dim3(kGThreads), 0, c->stream, (int)M, N, K, kps,
+                               E, Sp, Cpart);
             hipLaunchKernelGGL(k_zgemm_reduce, dim3((unsigned)((M * N + kNB - 1) / kNB)), dim3(kNB), 0, c->stream,
                                M * (size_t)N, nsplit, x0 == 0 ? 0 : 1, Cpart, Bp);
             DD_HIP(c, hipGetLastError());
