@@ -252,6 +252,7 @@ void dd_destroy(dd_ctx* c) {
     if (c->own_stream) (void)hipStreamDestroy(c->own_stream);
     if (c->host_state) (void)hipHostFree(c->host_state);
     if (c->host_dots) (void)hipHostFree(c->host_dots);
+    if (c->host_mask) (void)hipHostFree(c->host_mask);
     delete c;
 }
 

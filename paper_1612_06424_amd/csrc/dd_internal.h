@@ -162,6 +162,8 @@ struct dd_ctx {
     // pinned host mirrors of per-column state and of small reductions
     dd::ColState* host_state = nullptr;
     double* host_dots = nullptr;
+    int* host_mask = nullptr;  // two of host_n, used in turn
+    int mask_turn = 0;
     int host_n = 0;
     // fraction of a launch's columns whose spinor bytes the kernel timing bills: solvers set
     // it to the share of columns active when they launch (a stopped column's workgroups
@@ -305,9 +307,10 @@ enum Fin {
 // the second's results follow at out + 3 nseg).
 void launch_presum(dd_ctx* c, int nseg, SlotSum a, SlotSum b, double* out);
 
-// p0: device [nseg + 1] prefix of the partial slots of each segment.
+// p0: device [nseg + 1] prefix of the partial slots of each segment.  gate (may be null): the states that say
+// which segments run, in place of st; a sum that breaks down then leaves the segment's st running.
 void launch_finalize(dd_ctx* c, int fin, int nseg, const int* p0, const double* partial, ColState* st,
-                     double* out);
+                     double* out, const ColState* gate = nullptr);
 
 // The operator side of a solve: nseg independent systems M_k x_k = b_k.
 // apply runs the stencil of every segment in precision R with a fused

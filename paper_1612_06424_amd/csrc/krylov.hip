@@ -370,9 +370,9 @@ __global__ __launch_bounds__(kBlock) void k_zero_segs(Segs S, cpx<double>* __res
 // [p0[seg], p0[seg+1]), then the scalar recurrences of BiCGStab / CG for it.
 __global__ __launch_bounds__(kBlock) void k_finalize(int fin, const int* __restrict__ p0,
                                                      const double* __restrict__ partial, ColState* __restrict__ st,
-                                                     double* __restrict__ out) {
+                                                     double* __restrict__ out, const ColState* __restrict__ gate) {
     const int seg = blockIdx.x;
-    if (fin != FIN_STORE && !st[seg].active) return;
+    if (fin != FIN_STORE && !(gate ? gate : st)[seg].active) return;
     double d0 = 0, d1 = 0, d2 = 0;
     const int k0 = p0[seg], k1 = p0[seg + 1];
     for (int k = k0 + (int)threadIdx.x; k < k1; k += kBlock) {
@@ -453,7 +453,7 @@ __global__ __launch_bounds__(kBlock) void k_finalize(int fin, const int* __restr
             s.zz = d0;
             if (!(d0 > 0) || !isfinite(d0)) {
                 s.breakdown = isfinite(d0) ? 1 : 2;
-                s.active = 0;
+                if (!gate) s.active = 0;
             }
             break;
         }
@@ -534,8 +534,8 @@ void launch_zero_segs(dd_ctx* c, const Segs& S, cpx<double>* a, const int* mask)
 }
 
 void launch_finalize(dd_ctx* c, int fin, int nseg, const int* p0, const double* partial, ColState* st,
-                     double* out) {
-    hipLaunchKernelGGL(k_finalize, dim3((unsigned)nseg), dim3(kBlock), 0, c->stream, fin, p0, partial, st, out);
+                     double* out, const ColState* gate) {
+    hipLaunchKernelGGL(k_finalize, dim3((unsigned)nseg), dim3(kBlock), 0, c->stream, fin, p0, partial, st, out, gate);
 }
 
 #define DD_INST(R)                                                                                              \

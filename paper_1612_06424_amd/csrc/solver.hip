@@ -49,10 +49,13 @@ dd_status ensure_host(dd_ctx* c, int n) {
     if (c->host_n >= n) return DD_OK;
     if (c->host_state) (void)hipHostFree(c->host_state);
     if (c->host_dots) (void)hipHostFree(c->host_dots);
+    if (c->host_mask) (void)hipHostFree(c->host_mask);
     c->host_state = nullptr;
     c->host_dots = nullptr;
+    c->host_mask = nullptr;
     c->host_n = 0;
-    DD_HIP(c, hipHostMalloc((void**)&c->host_state, sizeof(ColState) * n, hipHostMallocDefault));
+    DD_HIP(c, hipHostMalloc((void**)&c->host_state, 2 * sizeof(ColState) * n, hipHostMallocDefault));
+    DD_HIP(c, hipHostMalloc((void**)&c->host_mask, 2 * sizeof(int) * n, hipHostMallocDefault));
     DD_HIP(c, hipHostMalloc((void**)&c->host_dots, sizeof(double) * 3 * n, hipHostMallocDefault));
     c->host_n = n;
     return DD_OK;
@@ -81,10 +84,13 @@ void bill_active(dd_ctx* c, int ns) {
     c->bill_frac = ns > 0 ? (double)n / ns : 1.0;
 }
 
-// Copy a per-segment mask from (pageable) host memory and wait for the copy.
+// Copy a per-segment mask to the device through pinned memory, without waiting for it.  The host waits for
+// the stream at least once (a residual or the states come back) between a call and the next but one,
+// so the copy out of a buffer is done before it is written again.
 dd_status push_mask(dd_ctx* c, int* dev, const std::vector<int>& mask) {
-    DD_HIP(c, hipMemcpyAsync(dev, mask.data(), sizeof(int) * mask.size(), hipMemcpyHostToDevice, c->stream));
-    DD_HIP(c, hipStreamSynchronize(c->stream));
+    int* buf = c->host_mask + (c->mask_turn ^= 1) * c->host_n;
+    std::memcpy(buf, mask.data(), sizeof(int) * mask.size());
+    DD_HIP(c, hipMemcpyAsync(dev, buf, sizeof(int) * mask.size(), hipMemcpyHostToDevice, c->stream));
     return DD_OK;
 }
 
@@ -311,7 +317,7 @@ dd_status bicgstab_reliable(System& S, const cpx<double>* b, cpx<double>* x, con
                 s.beta_re = s.beta_im = 0.0;
             }
         }
-        if (*nonfinite) break;
+        if (*nonfinite || ndone == ns) break;
         e = push_mask(c, W.mask_dev, mask);
         if (e != DD_OK) return e;
         launch_set_resid<R>(c, S.seg, W.r64, w.r, W.mask_dev);
@@ -458,23 +464,26 @@ dd_status cgnr_reliable(System& S, const cpx<double>* b, cpx<double>* x, const s
             s.breakdown = 0;
             rrmax[j] = rr;
         }
-        if (*nonfinite) break;
-        // recompute z = D^+ r for the updated segments only: mark them active
-        for (int j = 0; j < ns; j++) c->host_state[j].active = mask[j];
+        if (*nonfinite || ndone == ns) break;
+        // recompute z = D^+ r for the updated segments only: st2 marks them, st goes on with all running ones and
+        // takes up the new zz on the device
+        ColState* marked = c->host_state + ns;
+        for (int j = 0; j < ns; j++) {
+            marked[j] = c->host_state[j];
+            marked[j].active = mask[j];
+            c->host_state[j].active = mask[j];
+        }
+        bill_active(c, ns);
+        for (int j = 0; j < ns; j++) c->host_state[j].active = mask[j] ? 1 : keep_active[j];
         e = push_mask(c, W.mask_dev, mask);
         if (e != DD_OK) return e;
         launch_set_resid<R>(c, S.seg, W.r64, r, W.mask_dev);
         e = push_state(c, st, ns);
         if (e != DD_OK) return e;
-        bill_active(c, ns);
-        S.apply(1, EPI_NORM, r, tz, (const cpx<R>*)nullptr, partial, st);
-        launch_finalize(c, FIN_CG_ZZ, ns, S.sp0[kind], partial, st, nullptr);
+        DD_HIP(c, hipMemcpyAsync(st2, marked, sizeof(ColState) * ns, hipMemcpyHostToDevice, c->stream));
+        S.apply(1, EPI_NORM, r, tz, (const cpx<R>*)nullptr, partial, st2);
+        launch_finalize(c, FIN_CG_ZZ, ns, S.sp0[kind], partial, st, nullptr, st2);
         launch_cg_shift<R>(c, S.seg, pp, z, tz, W.mask_dev);
-        e = pull_state(c, st, ns);  // picks up the new zz
-        if (e != DD_OK) return e;
-        for (int j = 0; j < ns; j++) c->host_state[j].active = mask[j] ? 1 : keep_active[j];
-        e = push_state(c, st, ns);
-        if (e != DD_OK) return e;
     }
     res->iters = total;
     return DD_OK;
