@@ -234,9 +234,10 @@ void launch_dslash_sched(dd_ctx* c, const Geo& g, const StencilSched& sc, const 
                          int dag, int epi, const cpx<R>* in, cpx<R>* out, const cpx<R>* aux, int ncol,
                          double* partial, const ColState* st);
 // The stencil's LDS-tile form (dirac_tile.hip), tile flag bit 3 of a schedule with kc columns per
-// workgroup: usable on fields whose column is below 2 GiB; its partial slots per column.
+// workgroup: usable on fields whose column is below 2 GiB; its partial slots per column (bricks).
 bool dslash_lds_ok(const Geo& g, size_t real_bytes);
 int dslash_lds_blocks(const Geo& g);
+double dslash_lds_fill(const Geo& g);  // the share of the bricks' places that sites take
 template <typename R>
 void launch_dslash_lds(dd_ctx* c, const Geo& g, const StencilSched& sc, const cpx<R>* U, R mass, int dag, int epi,
                        const cpx<R>* in, cpx<R>* out, const cpx<R>* aux, int ncol, double* partial,

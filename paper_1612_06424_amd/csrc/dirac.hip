@@ -119,8 +119,20 @@ int brick_rows(const Geo& g, int nt) {
 // rule, us: 16 x 4^3 FP64 1 column 29.9 and 6.2; 11 x 15^3 FP32 5 columns 42.6 and 22.3; 16 x 16^3 FP64 1
 // column 42 and 16.6, 3 columns 49 and 31.6 (4 slices; 1 slice 40); 16 x 8^3 FP64 12 columns 39 and 16.7
 // (2 slices; 1 slice 19.2).  XCD-contiguous workgroups: 22.3 us against 34 for the 11 x 15^3 case.
+// The LDS-tile form with all columns in one group takes over where its bricks give every CU two
+// workgroups and leave little of them empty, us: 16 x 16^3 (512 bricks) FP64 1 column 16.6 and 15.4, 3 columns 31.9 and
+// 27.3, FP32 20.1 and 16.4; 7 x 32^3 FP32 32.1 and 28.1; but 30 x 19^3 FP64 (a quarter empty) 47.4 and 50.8, 16 x 8^3
+// with 12 columns (64 bricks) 16.6 and 45.9.
 StencilSched default_sched(const Geo& g, int kind, int ncol) {
     StencilSched sc;
+    if (dslash_lds_ok(g, kind == 0 ? 8 : 4) && dslash_lds_blocks(g) >= 512 && dslash_lds_fill(g) >= 0.9) {
+        sc.nt = 256;
+        sc.tc = 1;
+        sc.remap = 1;
+        sc.kc = ncol;
+        sc.blocked = 8;
+        return sc;
+    }
     sc.nt = 128;
     const size_t waves = (size_t)g.nsite * ncol / kWave, fit = kind == 0 ? 1024 : 4096;
     sc.tc = 1;
