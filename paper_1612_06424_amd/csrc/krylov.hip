@@ -9,8 +9,8 @@
 // their work; the reliable-update helpers are selected by a per-segment mask.
 //
 // Reductions are deterministic: every workgroup writes its FP64 partial sums
-// to a fixed slot and k_finalize adds a segment's slots in a fixed order, so
-// results are bitwise reproducible run to run.
+// to a fixed slot and k_finalize, or every workgroup that needs the sum, adds a
+// segment's slots in a fixed order, so results are bitwise reproducible run to run.
 #include <cmath>
 
 #include "dd_internal.h"

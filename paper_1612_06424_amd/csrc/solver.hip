@@ -3,8 +3,8 @@
 // stencil launch serves every segment and the vector kernels cover them all.
 //
 // The scalars of each segment live on the device (ColState) and are updated by
-// one-workgroup-per-segment finalize kernels, so iterations run without host
-// round trips; the host reads the per-segment state every `check_every`
+// one-workgroup-per-segment finalize kernels (BiCGStab) or the vector kernels
+// themselves (CGNR), so iterations run without host round trips; the host reads the per-segment state every `check_every`
 // iterations.  A System may ask for those inner iterations to be captured
 // once into a HIP graph and replayed.
 //

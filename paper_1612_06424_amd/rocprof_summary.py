@@ -32,8 +32,9 @@ import sys
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 # the sources that decide what the stencil kernels do and how they are launched
-STENCIL_SOURCES = ["csrc/dd_dslash.h", "csrc/dd_eo.h", "csrc/dd_eo_tile.h", "csrc/dd_wilson.h", "csrc/dd_internal.h",
-                   "csrc/dirac.hip", "csrc/evenodd.hip", "csrc/batched.hip", "csrc/tune.hip", "tune_cache_mi355x.txt"]
+STENCIL_SOURCES = ["csrc/dd_dslash.h", "csrc/dd_dslash_tile.h", "csrc/dd_eo.h", "csrc/dd_eo_tile.h", "csrc/dd_wilson.h",
+                   "csrc/dd_internal.h", "csrc/dirac.hip", "csrc/dirac_tile.hip", "csrc/evenodd.hip", "csrc/batched.hip",
+                   "csrc/tune.hip", "tune_cache_mi355x.txt"]
 
 
 def kernel_source_hash() -> str:
@@ -86,7 +87,7 @@ stencil,solve,fact,batched,force` and SEL = `--kernel-include-regex "dslash|eo_h
 
 Kernel names: `k_dslash<real, dagger, epilogue, workgroup size, columns per thread, x hops from
 neighbouring lanes>` is the time-sweep stencil (its HIP-event name omits the last argument, and the
-column count when it is 1) (epilogue 0 store, 1 <aux, D in>, 2 <D in, in> and |D in|^2, 3 residual,
+column count when it is 1), `k_dslash_lds<real, epilogue>` its LDS-tile form (epilogue 0 store, 1 <aux, D in>, 2 <D in, in> and |D in|^2, 3 residual,
 4 |D in|^2, 5 kappa D_hop in); `k_eo_hop<real, dagger, epilogue, workgroup size, self, columns per
 thread, two-row links>` is the even-odd half hop (`k_eo_hop_nt` the same with non-temporal output
 stores; self = true: the second half of the Schur operator, or the source preparation /
