@@ -11,7 +11,8 @@
 // so two workgroups share a CU and fill each other's waits: with 256 sites and one workgroup of 512
 // threads per CU D on 64 x 32^3, 12 columns, took 3472 us in FP64 and 1924 in FP32, this form 3146 and
 // 1870, the sweep 4160 and 2208; on 32 x 16^3 185 and 99 us against 266 and 137.  Time blocks of 8
-// bricks (FP64 on 64 x 32^3: 4 bricks 3444 us, 8 3146, 16 3688).  Where an FP64 and a loading-form sweep
+// bricks (FP64 on 64 x 32^3: 4 bricks 3444 us, 8 3146, 16 3688).  Clearing the links of dropped hops, which
+// may hold anything, costs FP64 2 % of that (3163 -> 3230 us through the library).  Where an FP64 and a loading-form sweep
 // give the same bits, this form gives them too.
 #pragma once
 
@@ -231,8 +232,8 @@ __device__ __forceinline__ void dslash_lds_body(const Geo& g, const EoTile& ts, 
         link(1, sl + ((x == 0) ? (L - 1) : -1), w3);
 #pragma unroll
         for (int k = 0; k < 9; k++) {
-            w0[k] = phf * w0[k];
-            w1[k] = phb * w1[k];
+            w0[k] = phf != R(0) ? phf * w0[k] : mk<R>(0, 0);  // the link of a dropped hop may hold anything
+            w1[k] = phb != R(0) ? phb * w1[k] : mk<R>(0, 0);
         }
         const int ixp = row * L + (x == L - 1 ? 0 : x + 1), ixm = row * L + (x == 0 ? L - 1 : x - 1);
         for (;;) {

@@ -407,8 +407,8 @@ __device__ __forceinline__ void eo_tile_body(const Geo& g, const EoTile& ts, con
         // the factor of the time edge goes into the link
 #pragma unroll
         for (int k = 0; k < 9; k++) {
-            w0[k] = phf * w0[k];
-            w1[k] = phb * w1[k];
+            w0[k] = phf != R(0) ? phf * w0[k] : mk<R>(0, 0);  // the link of a dropped hop may hold anything
+            w1[k] = phb != R(0) ? phb * w1[k] : mk<R>(0, 0);
         }
         const int ixp = row * LH + (bo ? (xh + 1 == LH ? 0 : xh + 1) : xh);
         const int ixm = row * LH + (bo ? xh : (xh == 0 ? LH - 1 : xh - 1));
