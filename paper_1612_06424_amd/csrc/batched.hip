@@ -667,9 +667,11 @@ dd_status solve_batch_eo(dd_ctx* c, const std::vector<Item>& its, const dd_solve
                 if (it.ncol % kc != 0) return false;
             return true;
         };
+        bool tile_ok = true;  // every domain's bricks fit (one launch serves them all)
+        for (const Item& it : its) tile_ok = tile_ok && eo_tile_ok(it.g.L, it.g.nt);
         const auto hit = c->sched.find(key);
         if (hit != c->sched.end() &&
-            ((hit->second.blocked & 8) ? hit->second.kc >= 1 : kc_ok(hit->second.kc))) {
+            ((hit->second.blocked & 8) ? tile_ok && hit->second.kc >= 1 : kc_ok(hit->second.kc))) {
             tc = hit->second.tc;
             rmap = hit->second.remap;
             kcb = hit->second.kc;
@@ -728,7 +730,7 @@ dd_status solve_batch_eo(dd_ctx* c, const std::vector<Item>& its, const dd_solve
             int widest = 0;
             for (const Item& it : its) widest = std::max(widest, it.ncol);
             for (int kc : {12, 6, 4, 2, 1})
-                if (e == DD_OK && (kc <= widest || kc == 12)) e = try_shape(1, kc, 8, 1);
+                if (e == DD_OK && tile_ok && (kc <= widest || kc == 12)) e = try_shape(1, kc, 8, 1);
             c->timing = saved;
             S.nblk = 0;  // launches size themselves from nblk64 / nblk32 again
             (void)hipEventDestroy(ea);

@@ -20,8 +20,6 @@
 
 namespace dd {
 
-constexpr int kDslSites = 128;             // sites of a workgroup at most
-constexpr int kDslHalo = 2 * kDslSites;    // halo sites of a workgroup at most
 constexpr int kDslNT = 2 * kDslSites;      // two threads per site
 
 template <typename R>
@@ -360,13 +358,6 @@ __device__ __forceinline__ void dslash_lds_body(const Geo& g, const EoTile& ts, 
         __syncthreads();
         write_sum();
     }
-}
-
-// Bricks of a field with x rows of L sites, in time blocks of 8.
-inline EoTile dslash_tile_shape(int L, int nt) {
-    EoTile t = tile_shape(L, L, nt, kDslSites, kDslHalo);
-    t.tb = t.ntt < 8 ? t.ntt : 8;
-    return t;
 }
 
 }  // namespace dd

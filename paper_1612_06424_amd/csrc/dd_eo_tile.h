@@ -29,18 +29,11 @@
 #include <type_traits>
 
 #include "dd_eo.h"
+#include "dd_tile_shape.h"
 
 namespace dd {
 
-constexpr int kTileSites = 256;               // output sites of a workgroup at most
 constexpr int kTileNT = 2 * kTileSites;       // two threads per output site
-
-// Brick of rt x rz x ry whole x rows (time, z, y) and the numbers of bricks per extent.
-struct EoTile {
-    int rt, ry, rz;
-    int ntt, nty, ntz;
-    int tb;  // bricks of a time block (consecutive workgroups)
-};
 
 // project / accum of dd_wilson.h with the sign as a factor f = +1 or -1 (the products are exact, so
 // the values are the same, and D and D^+ share one kernel).
@@ -524,31 +517,5 @@ __device__ __forceinline__ void eo_tile_body(const Geo& g, const EoTile& ts, con
         write_sum();
     }
 }
-
-// The bricks of a field of L^3 x nt whose x rows have `len` staged sites: of the shapes whose sites
-// and halo sites fit one workgroup, the one with the least workgroups and halo together (bricks at the end of an extent that they do not divide are cut short).  A time
-// block of 4 bricks keeps the slices that neighbouring workgroups read in one L2.
-inline EoTile tile_shape(int L, int len, int nt, int sites, int halo) {
-    EoTile best{1, 1, 1, nt, L, L, 1};
-    double score = 1e30;
-    for (int ry = 1; ry <= L; ry++)
-        for (int rz = 1; rz <= L; rz++) {
-            const int sl = ry * rz * len, hr = ((ry < L ? 2 * rz : 0) + (rz < L ? 2 * ry : 0)) * len;
-            if (sl > sites || hr > halo) continue;
-            int rt = sites / sl;
-            if (hr > 0 && halo / hr < rt) rt = halo / hr;
-            if (rt > nt) rt = nt;
-            const int nty = (L + ry - 1) / ry, ntz = (L + rz - 1) / rz, ntt = (nt + rt - 1) / rt;
-            const double sc = (double)nty * ntz * ntt * (sites + 0.5 * hr * rt);
-            if (sc < score) {
-                score = sc;
-                best = EoTile{rt, ry, rz, ntt, nty, ntz, 1};
-            }
-        }
-    best.tb = best.ntt < 4 ? best.ntt : 4;
-    return best;
-}
-inline EoTile eo_tile_shape(int L, int nt) { return tile_shape(L, L / 2, nt, kTileSites, kTileSites); }
-inline int eo_tile_blocks(const EoTile& t) { return t.ntt * t.nty * t.ntz; }
 
 }  // namespace dd

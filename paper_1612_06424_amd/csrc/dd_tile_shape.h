@@ -1,0 +1,64 @@
+// dd_tile_shape.h -- brick shapes of the LDS-tile forms of the half hop (dd_eo_tile.h) and of the stencil
+// (dd_dslash_tile.h), and the fields that the two forms take.  Host arithmetic only, without HIP, so that the
+// host tests compile it as it is.
+#pragma once
+
+#include <cstddef>
+
+namespace dd {
+
+constexpr int kTileSites = 256;            // half hop: output sites of a workgroup at most, and halo sites
+constexpr int kDslSites = 128;             // stencil: sites of a workgroup at most
+constexpr int kDslHalo = 2 * kDslSites;    // and halo sites
+
+// Brick of rt x rz x ry whole x rows (time, z, y) and the numbers of bricks per extent; all zero where no
+// brick fits.
+struct EoTile {
+    int rt, ry, rz;
+    int ntt, nty, ntz;
+    int tb;  // bricks of a time block (consecutive workgroups)
+};
+
+// The bricks of a field of L^3 x nt whose x rows have `len` staged sites: of the shapes whose sites
+// and halo sites fit one workgroup, the one with the least workgroups and halo together (bricks at the end of an
+// extent that they do not divide are cut short).  Rows too long for any (one row has four halo rows) give
+// none.  A time block of 4 bricks keeps the slices that neighbouring workgroups read in one L2.
+inline EoTile tile_shape(int L, int len, int nt, int sites, int halo) {
+    EoTile best{0, 0, 0, 0, 0, 0, 0};
+    double score = 1e30;
+    for (int ry = 1; ry <= L && ry * len <= sites; ry++)
+        for (int rz = 1; rz <= L && ry * rz * len <= sites; rz++) {
+            const int sl = ry * rz * len, hr = ((ry < L ? 2 * rz : 0) + (rz < L ? 2 * ry : 0)) * len;
+            if (hr > halo) continue;
+            int rt = sites / sl;
+            if (hr > 0 && halo / hr < rt) rt = halo / hr;
+            if (rt > nt) rt = nt;
+            const int nty = (L + ry - 1) / ry, ntz = (L + rz - 1) / rz, ntt = (nt + rt - 1) / rt;
+            const double sc = (double)nty * ntz * ntt * (sites + 0.5 * hr * rt);
+            if (sc < score) {
+                score = sc;
+                best = EoTile{rt, ry, rz, ntt, nty, ntz, 1};
+            }
+        }
+    best.tb = best.ntt < 4 ? best.ntt : 4;
+    return best;
+}
+inline bool tile_fits(const EoTile& t) { return t.rt > 0; }
+inline int eo_tile_blocks(const EoTile& t) { return t.ntt * t.nty * t.ntz; }
+
+// Half fields: rows of L / 2 sites.  A brick fits up to L = 128.
+inline EoTile eo_tile_shape(int L, int nt) { return tile_shape(L, L / 2, nt, kTileSites, kTileSites); }
+inline bool eo_tile_ok(int L, int nt) { return tile_fits(eo_tile_shape(L, nt)); }
+
+// Whole fields, in time blocks of 8.  A brick fits up to L = 64.
+inline EoTile dslash_tile_shape(int L, int nt) {
+    EoTile t = tile_shape(L, L, nt, kDslSites, kDslHalo);
+    t.tb = t.ntt < 8 ? t.ntt : 8;
+    return t;
+}
+// A dropped time hop is read from 2 GiB past the column's start, which has to lie outside the column.
+inline bool dslash_tile_ok(int L, int nt, size_t real_bytes) {
+    return (size_t)24 * nt * L * L * L * real_bytes < ((size_t)1 << 31) && tile_fits(dslash_tile_shape(L, nt));
+}
+
+}  // namespace dd

@@ -17,8 +17,7 @@ __global__ __launch_bounds__(kDslNT, 2) void k_dslash_lds(Geo g, EoTile ts, Tile
 
 }  // namespace
 
-// A dropped time hop is read from 2 GiB past the column's start, which has to lie outside the column.
-bool dslash_lds_ok(const Geo& g, size_t real_bytes) { return (size_t)24 * g.nsite * real_bytes < ((size_t)1 << 31); }
+bool dslash_lds_ok(const Geo& g, size_t real_bytes) { return dslash_tile_ok(g.L, g.nt, real_bytes); }
 
 int dslash_lds_blocks(const Geo& g) { return eo_tile_blocks(dslash_tile_shape(g.L, g.nt)); }
 double dslash_lds_fill(const Geo& g) { return (double)g.nsite / ((double)kDslSites * dslash_lds_blocks(g)); }

@@ -214,7 +214,7 @@ int eo_tile_cols(const Geo& g, int ncol) {
 // column on 32 x 16^3 10.9 and 11.2).
 StencilSched eo_default_sched(const Geo& g, int kind, int ncol) {
     const bool wide = ncol >= 4 && eo_tile_blocks(eo_tile_shape(g.L, g.nt)) >= 256;
-    if (kind == 1 || wide) {
+    if (eo_tile_ok(g.L, g.nt) && (kind == 1 || wide)) {
         const int kc = eo_tile_cols(g, ncol);
         return eo_tile_sched(ncol, (ncol + kc - 1) / kc);
     }
@@ -446,7 +446,14 @@ StencilSched eo_tune(dd_ctx* c, EOSystem& S, const cpx<R>* UR, const cpx<R>* UR1
                             std::to_string(g.L) + ":" + std::to_string(g.T) + ":" + std::to_string(g.nt) + ":" +
                             std::to_string(g.whole);
     const auto hit = c->sched.find(key);
-    if (hit != c->sched.end()) return hit->second;
+    if (hit != c->sched.end()) {
+        StencilSched sc = hit->second;
+        if ((sc.blocked & 8) && !eo_tile_ok(g.L, g.nt)) {  // a stored shape may name a form that does not fit the field
+            sc.blocked = 0;
+            sc.kc = 1;
+        }
+        return sc;
+    }
     StencilSched best = eo_default_sched(g, sizeof(R) == 8 ? 0 : 1, S.ncol);
     if ((size_t)g.nsite * S.ncol >= ((size_t)1 << 18)) {
         hipEvent_t a, b;
@@ -479,7 +486,7 @@ StencilSched eo_tune(dd_ctx* c, EOSystem& S, const cpx<R>* UR, const cpx<R>* UR1
             // the LDS-tile form: columns per workgroup
             const int kfill = eo_tile_cols(g, S.ncol);
             for (int parts : {1, 2, 3, (S.ncol + kfill - 1) / kfill}) {
-                if (parts > S.ncol) continue;
+                if (parts > S.ncol || !eo_tile_ok(g.L, g.nt)) continue;
                 StencilSched sc = eo_tile_sched(S.ncol, parts);
                 const float ms = time_shape(sc);
                 if (ms < best_ms) {

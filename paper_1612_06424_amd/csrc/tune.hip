@@ -149,7 +149,7 @@ StencilSched stencil_sched(dd_ctx* c, const Geo& g, int kind, int ncol) {
     const std::string k = key_of(g, kind, ncol);
     auto it = c->sched.find(k);
     if (it != c->sched.end()) {
-        StencilSched hit = it->second;  // (a stored shape may name a form that the field is too large for)
+        StencilSched hit = it->second;  // (a stored shape may name a form that does not fit the field)
         if ((hit.blocked & 8) && !dslash_lds_ok(g, kind == 0 ? 8 : 4)) hit.blocked = 0;
         return hit;
     }
