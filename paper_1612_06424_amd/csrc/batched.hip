@@ -372,6 +372,8 @@ struct BatchEOSystem : System {
     int kc[2] = {1, 1};                // columns per workgroup per precision
     bool lds[2] = {false, false};      // LDS-tile form per precision
     bool rec32 = false;                // FP32 descriptors carry two-row links
+    bool rec_tile = false;             // and the LDS-tile form reads them: even column counts only, as in
+                                       // the sweep with two columns (eo_two_rows)
     cpx<double>* tmp64 = nullptr;
     cpx<float>* tmp32 = nullptr;
 
@@ -382,7 +384,7 @@ struct BatchEOSystem : System {
         const int rm = remap[sizeof(R) == 8 ? 0 : 1];
         const int k = kc[sizeof(R) == 8 ? 0 : 1];
         const bool tile = lds[sizeof(R) == 8 ? 0 : 1];
-        const bool rec = sizeof(R) == 4 && rec32 && (tile || k > 1);
+        const bool rec = sizeof(R) == 4 && rec32 && (tile ? rec_tile : k > 1);
         for (int half = 0; half < 2; half++) {
             const int e = half ? epi : EPI_STORE;
             hipEvent_t ev = nullptr;
@@ -599,6 +601,8 @@ dd_status solve_batch_eo(dd_ctx* c, const std::vector<Item>& its, const dd_solve
     S.has32 = mixed;
     S.pair32 = true;  // FP32 half fields with paired components (dd_eo.h)
     S.rec32 = su3_all;
+    S.rec_tile = true;
+    for (const Item& it : its) S.rec_tile = S.rec_tile && it.ncol % 2 == 0;
     S.tmp64 = (cpx<double>*)workspace(c, W_EO_T64, (size_t)nhalf * sizeof(cpx<double>), &e);
     if (e != DD_OK) return e;
     if (mixed) {

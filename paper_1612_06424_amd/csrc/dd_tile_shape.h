@@ -49,6 +49,15 @@ inline int eo_tile_blocks(const EoTile& t) { return t.ntt * t.nty * t.ntz; }
 // Half fields: rows of L / 2 sites.  A brick fits up to L = 128.
 inline EoTile eo_tile_shape(int L, int nt) { return tile_shape(L, L / 2, nt, kTileSites, kTileSites); }
 inline bool eo_tile_ok(int L, int nt) { return tile_fits(eo_tile_shape(L, nt)); }
+// Whether an FP32 launch of the form may read two rows of a link and rebuild the third in FP32 (SU(3) links
+// only): fields whose launch is timed, with an even number of columns or the rows of L = 16 and 32.  The
+// rebuilt row is less exact than a stored one (rounding, and what the links are off SU(3)), so launches
+// that have always read nine entries go on doing so: small fields, and odd column counts at other L.  Two rows
+// in those too are faster (ms, two and nine: the one-column force on 32 x 16^3 19.6 and 21.5, the factorised
+// propagator on 16 x 4^3 8.3 and 8.9, a solve of three columns of 16 x 24^3 10.2 and 10.9).
+inline bool eo_two_rows(int L, int nt, int ncol) {
+    return (size_t)nt * L * L * L * ncol >= ((size_t)1 << 18) && (ncol % 2 == 0 || L == 16 || L == 32);
+}
 
 // Whole fields, in time blocks of 8.  A brick fits up to L = 64.
 inline EoTile dslash_tile_shape(int L, int nt) {

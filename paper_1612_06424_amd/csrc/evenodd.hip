@@ -317,7 +317,7 @@ void launch_eo_lds(hipStream_t s, int epi, bool sf, const Geo& g, const EoTile& 
 // bricks (pair_site) rather than rows, bit 1 the chunks of a tile adjacent,
 // bit 2 non-temporal output stores (k_eo_hop_nt; FP32 with kc > 1 only).
 // U: the checkerboard links; U12 (nullable): the same links as two rows each,
-// which launches with kc > 1 read instead.
+// which sweeps with kc > 1 and some LDS-tile launches (eo_two_rows) read instead.
 //
 // Tile flag bit 3 selects the LDS-tile form with kc columns per workgroup (its partial slots:
 // eo_slots); of its launches only those with a self field form sums.
@@ -328,7 +328,7 @@ void launch_eo_hop(dd_ctx* c, const Geo& g, const cpx<R>* U, const cpx<R>* U12, 
     const bool sf = self != nullptr && a_self != 0;
     if (blocked & 8) {
         const int cpw = std::max(1, std::min(kc, ncol));
-        const bool rec = U12 != nullptr;
+        const bool rec = U12 != nullptr && eo_two_rows(g.L, g.nt, ncol);
         const EoTile ts = eo_tile_shape(g.L, g.nt);
         EoTileArgs<R> a;
         a.U = rec ? U12 : U;
