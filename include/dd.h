@@ -402,7 +402,11 @@ dd_status dd_block_solve_batched(dd_ctx* ctx, int n, const dd_batch_item* items,
  * Stencil launch shapes are tuned per context on first use; with the
  * environment variable DD_TUNE_CACHE naming a file, contexts load the shapes
  * stored there and append new ones, so that separate processes launch the
- * same kernels.
+ * same kernels.  D (dd_apply_dirac) gives the same bits whatever shape the
+ * tuning picks: which of the two forms of its kernel runs depends on the sizes
+ * and the column count only (or on a stored shape that names one).  The sums
+ * of the solvers are grouped by the launch shape, so solutions of contexts
+ * that tuned differently agree to rounding.
  *
  * Kernel timing on the context stream.  With enable != 0 every stencil
  * launch made by the library is bracketed by HIP events recorded on the

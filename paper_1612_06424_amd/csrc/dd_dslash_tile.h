@@ -12,8 +12,9 @@
 // threads per CU D on 64 x 32^3, 12 columns, took 3472 us in FP64 and 1924 in FP32, this form 3146 and
 // 1870, the sweep 4160 and 2208; on 32 x 16^3 185 and 99 us against 266 and 137.  Time blocks of 8
 // bricks (FP64 on 64 x 32^3: 4 bricks 3444 us, 8 3146, 16 3688).  Clearing the links of dropped hops, which
-// may hold anything, costs FP64 2 % of that (3163 -> 3230 us through the library).  Where an FP64 and a loading-form sweep
-// give the same bits, this form gives them too.
+// may hold anything, costs FP64 2 % of that (3163 -> 3230 us through the library).  A site's hops are added
+// as (time and x) + (y and z), not one after the other as in the sweep, so the two forms agree to rounding;
+// which one a launch takes depends on its sizes only (dslash_tile_form).
 #pragma once
 
 #include "dd_eo_tile.h"

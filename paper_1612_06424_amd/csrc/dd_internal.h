@@ -233,11 +233,14 @@ template <typename R>
 void launch_dslash_sched(dd_ctx* c, const Geo& g, const StencilSched& sc, const cpx<R>* U, double kappa,
                          int dag, int epi, const cpx<R>* in, cpx<R>* out, const cpx<R>* aux, int ncol,
                          double* partial, const ColState* st);
+// Launches of fewer site-columns than this take default_sched, untimed.
+inline bool stencil_timed(const Geo& g, int ncol) { return (size_t)g.nsite * ncol >= ((size_t)1 << 18); }
 // The stencil's LDS-tile form (dirac_tile.hip), tile flag bit 3 of a schedule with kc columns per
-// workgroup: usable on fields whose column is below 2 GiB; its partial slots per column (bricks).
+// workgroup: whether a field can take it (a brick fits, a column is below 2 GiB), whether a launch does
+// where no stored shape says otherwise, its partial slots per column (bricks).
 bool dslash_lds_ok(const Geo& g, size_t real_bytes);
+bool dslash_lds_form(const Geo& g, size_t real_bytes, int ncol);
 int dslash_lds_blocks(const Geo& g);
-double dslash_lds_fill(const Geo& g);  // the share of the bricks' places that sites take
 template <typename R>
 void launch_dslash_lds(dd_ctx* c, const Geo& g, const StencilSched& sc, const cpx<R>* U, R mass, int dag, int epi,
                        const cpx<R>* in, cpx<R>* out, const cpx<R>* aux, int ncol, double* partial,

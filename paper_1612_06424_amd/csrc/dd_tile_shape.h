@@ -70,4 +70,26 @@ inline bool dslash_tile_ok(int L, int nt, size_t real_bytes) {
     return (size_t)24 * nt * L * L * L * real_bytes < ((size_t)1 << 31) && tile_fits(dslash_tile_shape(L, nt));
 }
 
+
+// Whether a launch on a field takes the form: by sizes alone, not by a timing, since the form adds the hops of a
+// site in another order than the sweep and a result must not depend on how two launches happened to be
+// timed (the launch shapes within a form give the same bits).  `timed`: the shape is timed, the best of each form
+// compared below (us, sweep and form); else the untimed shapes (default_sched).
+// Untimed: bricks that give every CU two workgroups and are nearly full.
+// FP64: bricks three quarters full win with one column too (32 x 24^3 113 and 104, 64 x 32^3 1.00; 12 columns of
+// 6 x 16^3, 192 bricks, 51.9 and 44.3; but 4 of 32 x 14^3 58 and 61); down to 0.6 with columns to share the links (8 x
+// 40^3, 2 columns 209 and 223, 6 columns 590 and 551); below that never (8 x 48^3, 12 columns 2068 and 2518).
+// FP32 moves half the bytes past the same instructions, so one column never pays (64 x 32^3 1.18 of the
+// sweep's time); from two on full bricks do (8 x 32^3 46.7 and 42.3), others with several columns and bricks
+// enough (4 columns of 32 x 24^3 188 and 174, of 48 x 12^3, 768 bricks, 1.05) or with all twelve (16 x 18^3 0.89).
+inline bool dslash_tile_form(int L, int nt, int ncol, size_t real_bytes, bool timed) {
+    if (!dslash_tile_ok(L, nt, real_bytes)) return false;
+    const int bricks = eo_tile_blocks(dslash_tile_shape(L, nt));
+    const double fill = (double)nt * L * L * L / ((double)kDslSites * bricks);
+    if (!timed) return bricks >= 512 && fill >= 0.9;
+    if (bricks < 192) return false;
+    if (real_bytes == 8) return fill >= 0.75 || (fill >= 0.6 && ncol >= 6);
+    return ncol >= 2 && (fill >= 0.87 || (ncol >= 4 && fill >= 0.75 && bricks >= 1024) || (ncol >= 12 && fill >= 0.8));
+}
+
 }  // namespace dd

@@ -113,19 +113,19 @@ int brick_rows(const Geo& g, int nt) {
     return ry;
 }
 
-// Shape of a launch too small to be tuned (kind 0: FP64, 1: FP32).  A sweep over tc slices is a
-// serial chain of about 2 us a slice, so the chunks are as short as the wavefronts that run at
-// once allow: 1024 in FP64 (one a SIMD), 4096 in FP32.  Chunks of 8 slices in hardware order, and this
+// Shape of a launch too small to be timed, or of one whose timing found no memory (kind 0: FP64, 1: FP32).  Of
+// the sweep: a chunk of tc slices is a serial chain of about 2 us a slice, so the chunks are as short as the
+// wavefronts that run at once allow: 1024 in FP64 (one a SIMD), 4096 in FP32.  Below the timing's
+// threshold that is 1, 2 or 4 slices in FP64 and 1 in FP32.  Chunks of 8 slices in hardware order, and this
 // rule, us: 16 x 4^3 FP64 1 column 29.9 and 6.2; 11 x 15^3 FP32 5 columns 42.6 and 22.3; 16 x 16^3 FP64 1
 // column 42 and 16.6, 3 columns 49 and 31.6 (4 slices; 1 slice 40); 16 x 8^3 FP64 12 columns 39 and 16.7
 // (2 slices; 1 slice 19.2).  XCD-contiguous workgroups: 22.3 us against 34 for the 11 x 15^3 case.
-// The LDS-tile form with all columns in one group takes over where its bricks give every CU two
-// workgroups and leave little of them empty, us: 16 x 16^3 (512 bricks) FP64 1 column 16.6 and 15.4, 3 columns 31.9 and
-// 27.3, FP32 20.1 and 16.4; 7 x 32^3 FP32 32.1 and 28.1; but 30 x 19^3 FP64 (a quarter empty) 47.4 and 50.8, 16 x 8^3
-// with 12 columns (64 bricks) 16.6 and 45.9.
+// The LDS-tile form (dslash_tile_form) takes all columns in one group, us, sweep and form: 16 x 16^3 FP64 1 column 16.6
+// and 15.4, 3 columns 31.9 and 27.3, FP32 20.1 and 16.4; 7 x 32^3 FP32 32.1 and 28.1; but 30 x 19^3 FP64 (a
+// quarter empty) 47.4 and 50.8, 16 x 8^3 with 12 columns (64 bricks) 16.6 and 45.9.
 StencilSched default_sched(const Geo& g, int kind, int ncol) {
     StencilSched sc;
-    if (dslash_lds_ok(g, kind == 0 ? 8 : 4) && dslash_lds_blocks(g) >= 512 && dslash_lds_fill(g) >= 0.9) {
+    if (dslash_lds_form(g, kind == 0 ? 8 : 4, ncol)) {
         sc.nt = 256;
         sc.tc = 1;
         sc.remap = 1;

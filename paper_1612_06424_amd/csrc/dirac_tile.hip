@@ -19,8 +19,11 @@ __global__ __launch_bounds__(kDslNT, 2) void k_dslash_lds(Geo g, EoTile ts, Tile
 
 bool dslash_lds_ok(const Geo& g, size_t real_bytes) { return dslash_tile_ok(g.L, g.nt, real_bytes); }
 
+bool dslash_lds_form(const Geo& g, size_t real_bytes, int ncol) {
+    return dslash_tile_form(g.L, g.nt, ncol, real_bytes, stencil_timed(g, ncol));
+}
+
 int dslash_lds_blocks(const Geo& g) { return eo_tile_blocks(dslash_tile_shape(g.L, g.nt)); }
-double dslash_lds_fill(const Geo& g) { return (double)g.nsite / ((double)kDslSites * dslash_lds_blocks(g)); }
 
 template <typename R>
 void launch_dslash_lds(dd_ctx* c, const Geo& g, const StencilSched& sc, const cpx<R>* U, R mass, int dag, int epi,

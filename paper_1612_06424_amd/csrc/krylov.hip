@@ -10,7 +10,8 @@
 //
 // Reductions are deterministic: every workgroup writes its FP64 partial sums
 // to a fixed slot and k_finalize, or every workgroup that needs the sum, adds a
-// segment's slots in a fixed order, so results are bitwise reproducible run to run.
+// segment's slots in a fixed order, so results are bitwise reproducible run to run
+// for given launch shapes (the slots of the stencil's sums are those of its launch, whose shape may be timed).
 #include <cmath>
 
 #include "dd_internal.h"

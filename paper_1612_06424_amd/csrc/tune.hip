@@ -5,9 +5,11 @@
 // lattice geometry (how many
 // workgroups are resident per XCD against how much of the 4 MB L2 one time
 // slice of them touches).  The first launch for a new key times every
-// candidate on scratch buffers of the same size (best of three timings) and
-// keeps the fastest; later
-// launches reuse it.  Small problems use the default shape untimed.
+// candidate of its form on scratch buffers of the same size (best of three timings)
+// and keeps the fastest; later launches reuse it.  Small problems use the default
+// shape untimed.  Which form a launch takes (the sweep or the LDS tile) depends on its
+// sizes only (dslash_tile_form), and the shapes of a form differ in nothing but
+// speed, so a timing never decides a bit of D's result.
 //
 // With the environment variable DD_TUNE_CACHE naming a file, a new context
 // loads the choices stored there and every new choice is appended to it, so
@@ -78,18 +80,15 @@ StencilSched tune(dd_ctx* c, const Geo& g, int ncol) {
         }
     };
     // the LDS-tile form, the columns in 1 to 3 groups
-    for (int parts = 1; parts <= 3 && parts <= ncol && dslash_lds_ok(g, sizeof(R)); parts++) {
-        StencilSched sc;
-        sc.nt = 256;
-        sc.tc = 1;
-        sc.remap = 1;
+    const bool tile = (best.blocked & 8) != 0;
+    for (int parts = 1; tile && parts <= 3 && parts <= ncol; parts++) {
+        StencilSched sc = best;
         sc.kc = (ncol + parts - 1) / parts;
-        sc.blocked = 8;
         time_shape(sc);
     }
     const int tcs[] = {1, 2, 4, 8, 16, 1 << 20};
     const bool large = (size_t)g.nsite * ncol > (size_t)1 << 21;  // short chunks only fill the chip on smaller fields
-    for (int kc = 1; kc <= 4; kc++)
+    for (int kc = 1; !tile && kc <= 4; kc++)
     for (int nt : {128, 256})
         for (int tcv : tcs)
             for (int remap : {0, 1})
@@ -154,7 +153,7 @@ StencilSched stencil_sched(dd_ctx* c, const Geo& g, int kind, int ncol) {
         return hit;
     }
     StencilSched sc = default_sched(g, kind, ncol);
-    if (c->autotune && (size_t)g.nsite * ncol >= ((size_t)1 << 18))
+    if (c->autotune && stencil_timed(g, ncol))
         sc = kind == 0 ? tune<double>(c, g, ncol) : tune<float>(c, g, ncol);
     tune_cache_store(c, k, sc);
     return sc;

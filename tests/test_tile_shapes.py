@@ -22,6 +22,8 @@ void dslash_shape(int L, int nt, int* s) { dd::EoTile t = dd::dslash_tile_shape(
     int v[7] = {t.rt, t.ry, t.rz, t.ntt, t.nty, t.ntz, t.tb}; for (int k = 0; k < 7; k++) s[k] = v[k]; }
 int eo_ok(int L, int nt) { return dd::eo_tile_ok(L, nt); }
 int dslash_ok(int L, int nt, int bytes) { return dd::dslash_tile_ok(L, nt, (size_t)bytes); }
+int dslash_form(int L, int nt, int ncol, int bytes, int timed) {
+    return dd::dslash_tile_form(L, nt, ncol, (size_t)bytes, timed != 0); }
 void limits(int* s) { s[0] = dd::kTileSites; s[1] = dd::kDslSites; s[2] = dd::kDslHalo; }
 }
 """
@@ -75,3 +77,19 @@ def test_accepted_shapes_fit_and_the_others_are_refused(shapes):
                 _check(s, L, L, nt, sites, halo)
             else:
                 assert s == [0] * 7
+
+
+def test_the_stencil_takes_the_form_only_where_it_fits(shapes):
+    """The rule that picks the form (by sizes alone) over every L, on both sides of the timing's threshold."""
+    taken = 0
+    for L in range(2, 196):
+        for nt in NTS:
+            if nt * L ** 3 * 144 >= 2 ** 31:
+                continue
+            for nbytes in (4, 8):
+                for ncol in (1, 2, 4, 6, 12, 48):
+                    timed = nt * L ** 3 * ncol >= 2 ** 18
+                    if shapes.dslash_form(L, nt, ncol, nbytes, int(timed)):
+                        assert shapes.dslash_ok(L, nt, nbytes), (L, nt, ncol, nbytes)
+                        taken += 1
+    assert taken > 0
