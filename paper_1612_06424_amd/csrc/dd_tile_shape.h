@@ -49,6 +49,32 @@ inline int eo_tile_blocks(const EoTile& t) { return t.ntt * t.nty * t.ntz; }
 // Half fields: rows of L / 2 sites.  A brick fits up to L = 128.
 inline EoTile eo_tile_shape(int L, int nt) { return tile_shape(L, L / 2, nt, kTileSites, kTileSites); }
 inline bool eo_tile_ok(int L, int nt) { return tile_fits(eo_tile_shape(L, nt)); }
+// Columns per workgroup that put all columns of a field into one round of workgroups, one to each of the 256
+// CUs (a workgroup fills a CU's register file), or all columns of a brick into one where the bricks alone are more.
+inline int eo_tile_cols(int L, int nt, int ncol) {
+    const int bricks = eo_tile_blocks(eo_tile_shape(L, nt));
+    const int groups = bricks > 0 && bricks <= 256 ? 256 / bricks : 1;
+    return groups < ncol ? (ncol + groups - 1) / groups : 1;
+}
+
+// Whether an untimed launch takes the form.  FP32: where one round of workgroups holds it, with a column each or, in
+// full bricks, several one after the other; a second round costs more than the sweep's shorter workgroups.
+// Mixed solves, ms, form and sweep of one slice per chunk: one column of 32 x 16^3 (256 bricks) 3.46 and 3.56, of 8 x 24^3
+// (240) 3.21 and 3.26, of 6 x 28^3 (294) 4.43 and 3.96, of 6 x 32^3 (384) 5.15 and 4.52; 12 columns of 16 x 4^3 2.47 and
+// 2.60; 9 of 16 x 12^3 (64) 4.48 and 4.95; 3 of 4 x 26^3 (180, three quarters full) 3.76 and 3.52; on the wrong side 5 of
+// 8 x 18^3 (96 bricks, three columns one after the other) 4.61 and 4.27, 6 of 20 x 10^3 3.41 and 3.13.
+// FP64: where a whole workgroup per CU has columns to loop over and the bricks are full (us a half hop, 12 columns:
+// 16 x 32^3, 1024 bricks, 418 against the sweep's 579; 32 x 16^3, 256 bricks, 86 against 140; 8 x 16^3, 64 bricks, 36
+// against 31; solves, ms: 4 columns of 16 x 20^3 14.3 and 16.6, 12 of 4 x 40^3, 0.64 full, 85 and 74, 4 of 2 x 96^3, 0.38 full,
+// 302 and 142).
+inline bool eo_tile_form(int L, int nt, int ncol, size_t real_bytes) {
+    const int bricks = eo_tile_blocks(eo_tile_shape(L, nt));
+    if (bricks == 0) return false;
+    const double fill = 0.5 * nt * L * L * L / ((double)kTileSites * bricks);
+    if (real_bytes == 8) return ncol >= 4 && bricks >= 256 && fill >= 0.8;
+    return bricks <= 256 && ((long long)bricks * ncol <= 256 || fill >= 0.8);
+}
+
 // Whether an FP32 launch of the form may read two rows of a link and rebuild the third in FP32 (SU(3) links
 // only): fields whose launch is timed, with an even number of columns or the rows of L = 16 and 32.  The
 // rebuilt row is less exact than a stored one (rounding, and what the links are off SU(3)), so launches

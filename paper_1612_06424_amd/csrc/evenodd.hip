@@ -195,27 +195,15 @@ StencilSched eo_tile_sched(int ncol, int parts) {
     return sc;
 }
 
-// Columns per workgroup of the LDS-tile form that leave about one workgroup per CU.
-int eo_tile_cols(const Geo& g, int ncol) {
-    const int tiles = eo_tile_blocks(eo_tile_shape(g.L, g.nt));
-    return std::max(1, std::min(ncol, (int)(((size_t)ncol * tiles + 255) / 256)));
-}
-
-// The shape of a launch that is not tuned (kind 0: FP64, 1: FP32).
-// FP32 takes the LDS-tile form, columns looped over only past one workgroup per CU.  Solves of 16 x 8^3
-// with 12 columns (16 bricks) take 14.6 ms with 12 columns per workgroup, 9.4 with 6 and 5.1 with 1; 16 x 16^3 with 3
-// (128 bricks) 8.8 with 3, 8.4 with 2 and 9.7 with 1; the sweep of one slice per chunk 6.0 and 9.7.
-// FP64 does so only where a whole workgroup per CU has columns to loop over (12 columns: 16 x 32^3, 1024
-// bricks, 418 us against the sweep's 579; 32 x 16^3, 256 bricks, 86 against 140; 8 x 16^3, 64 bricks, 36
-// against 31).  Below that the sweep of one slice per chunk, one column per thread: the most workgroups and
+// The shape of a launch that is not tuned (kind 0: FP64, 1: FP32): the LDS-tile form where eo_tile_form says, else
+// the sweep of one slice per chunk, one column per thread: the most workgroups and
 // the shortest serial chain (one column on 32 x 16^3, chunks of 1 and 4 slices: 17.7 and 36 us),
-// with bricks, a brick's slices adjacent and contiguous work per XCD, which the L2 caches need (solves:
+// with bricks, a brick's slices adjacent and contiguous work per XCD, which the L2 caches need (FP64 solves:
 // 16 x 16^3 with 3 columns 12.5 ms against 15.8 in hardware order, 20 x 10^3 with 6 columns 8.0 and 9.8, one
 // column on 32 x 16^3 10.9 and 11.2).
 StencilSched eo_default_sched(const Geo& g, int kind, int ncol) {
-    const bool wide = ncol >= 4 && eo_tile_blocks(eo_tile_shape(g.L, g.nt)) >= 256;
-    if (eo_tile_ok(g.L, g.nt) && (kind == 1 || wide)) {
-        const int kc = eo_tile_cols(g, ncol);
+    if (eo_tile_form(g.L, g.nt, ncol, kind == 0 ? 8 : 4)) {
+        const int kc = eo_tile_cols(g.L, g.nt, ncol);
         return eo_tile_sched(ncol, (ncol + kc - 1) / kc);
     }
     StencilSched sc;
@@ -484,7 +472,7 @@ StencilSched eo_tune(dd_ctx* c, EOSystem& S, const cpx<R>* UR, const cpx<R>* UR1
                 return ms;
             };
             // the LDS-tile form: columns per workgroup
-            const int kfill = eo_tile_cols(g, S.ncol);
+            const int kfill = eo_tile_cols(g.L, g.nt, S.ncol);
             for (int parts : {1, 2, 3, (S.ncol + kfill - 1) / kfill}) {
                 if (parts > S.ncol || !eo_tile_ok(g.L, g.nt)) continue;
                 StencilSched sc = eo_tile_sched(S.ncol, parts);

@@ -24,6 +24,8 @@ int eo_ok(int L, int nt) { return dd::eo_tile_ok(L, nt); }
 int dslash_ok(int L, int nt, int bytes) { return dd::dslash_tile_ok(L, nt, (size_t)bytes); }
 int dslash_form(int L, int nt, int ncol, int bytes, int timed) {
     return dd::dslash_tile_form(L, nt, ncol, (size_t)bytes, timed != 0); }
+int eo_form(int L, int nt, int ncol, int bytes) { return dd::eo_tile_form(L, nt, ncol, (size_t)bytes); }
+int eo_cols(int L, int nt, int ncol) { return dd::eo_tile_cols(L, nt, ncol); }
 void limits(int* s) { s[0] = dd::kTileSites; s[1] = dd::kDslSites; s[2] = dd::kDslHalo; }
 }
 """
@@ -93,3 +95,27 @@ def test_the_stencil_takes_the_form_only_where_it_fits(shapes):
                         assert shapes.dslash_ok(L, nt, nbytes), (L, nt, ncol, nbytes)
                         taken += 1
     assert taken > 0
+
+
+def test_the_untimed_half_hop_takes_the_form_only_where_it_fits(shapes):
+    """FP32: in one round of at most 256 workgroups; FP64: in 256 bricks or more."""
+    taken = {4: 0, 8: 0}
+    for L in range(2, 196, 2):
+        for nt in NTS:
+            if nt * L ** 3 * 144 >= 2 ** 31:
+                continue
+            for ncol in (1, 2, 3, 5, 12):
+                for nbytes in (4, 8):
+                    if not shapes.eo_form(L, nt, ncol, nbytes):
+                        continue
+                    taken[nbytes] += 1
+                    assert shapes.eo_ok(L, nt)
+                    s, kc = _shape(shapes.eo_shape, L, nt), shapes.eo_cols(L, nt, ncol)
+                    bricks = s[3] * s[4] * s[5]
+                    assert 1 <= kc <= ncol
+                    if nbytes == 4:
+                        assert bricks * -(-ncol // kc) <= 256
+                        assert kc == 1 or bricks * -(-ncol // (kc - 1)) > 256, "as many workgroups as fit"
+                    else:
+                        assert bricks >= 256 and ncol >= 4 and kc == ncol
+    assert min(taken.values()) > 0
