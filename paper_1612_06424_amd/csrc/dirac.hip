@@ -114,12 +114,14 @@ int brick_rows(const Geo& g, int nt) {
 }
 
 // Shape of a launch too small to be timed, or of one whose timing found no memory (kind 0: FP64, 1: FP32).  Of
-// the sweep: a chunk of tc slices is a serial chain of about 2 us a slice, so the chunks are as short as the
-// wavefronts that run at once allow: 1024 in FP64 (one a SIMD), 4096 in FP32.  Below the timing's
-// threshold that is 1, 2 or 4 slices in FP64 and 1 in FP32.  Chunks of 8 slices in hardware order, and this
-// rule, us: 16 x 4^3 FP64 1 column 29.9 and 6.2; 11 x 15^3 FP32 5 columns 42.6 and 22.3; 16 x 16^3 FP64 1
-// column 42 and 16.6, 3 columns 49 and 31.6 (4 slices; 1 slice 40); 16 x 8^3 FP64 12 columns 39 and 16.7
-// (2 slices; 1 slice 19.2).  XCD-contiguous workgroups: 22.3 us against 34 for the 11 x 15^3 case.
+// the sweep: a chunk of tc slices is a serial chain of tc + 1 steps of 2 to 6 us (its first slice loads its
+// backward neighbours too), and the workgroups run in rounds of 512 in FP64 (one wavefront a SIMD), 2048 in
+// FP32, so the chunk is taken that makes rounds times steps least.  us, chunks of 8 slices in hardware order, of 1 to 4 by the mean
+// wavefronts per SIMD, and so: 16 x 4^3 FP64 1 column 29.9, 6.2, 6.2; 11 x 15^3 FP32 5 columns 42.6, 22.3, 22.3; 16 x 8^3
+// FP64 12 columns 39.9, 17.6, 17.6; 9 x 13^3 FP64 12 columns 53.5, 67.9 (two rounds of 4 slices, the second nearly
+// empty), 46.3; 6 x 11^3 FP64 24 columns 35.6, 60.5, 37.9.
+// Workgroups in XCD-contiguous ranges (22.3 us against 34 for the 11 x 15^3 case), but in hardware order where the
+// columns are a larger multiple of 8: each XCD then keeps to the same columns (24 columns of 6 x 11^3 38.7 and 42.5).
 // The LDS-tile form (dslash_tile_form) takes all columns in one group, us, sweep and form: 16 x 16^3 FP64 1 column 16.6
 // and 15.4, 3 columns 31.9 and 27.3, FP32 20.1 and 16.4; 7 x 32^3 FP32 32.1 and 28.1; but 30 x 19^3 FP64 (a
 // quarter empty) 47.4 and 50.8, 16 x 8^3 with 12 columns (64 bricks) 16.6 and 45.9.
@@ -134,11 +136,16 @@ StencilSched default_sched(const Geo& g, int kind, int ncol) {
         return sc;
     }
     sc.nt = 128;
-    const size_t waves = (size_t)g.nsite * ncol / kWave, fit = kind == 0 ? 1024 : 4096;
-    sc.tc = 1;
-    while (sc.tc < g.nt && sc.tc < 8 && waves > fit * sc.tc) sc.tc *= 2;
-    sc.tc = sc.tc < g.nt ? sc.tc : g.nt;
-    sc.remap = 1;
+    const size_t tiles = (size_t)((g.L3 + sc.nt - 1) / sc.nt) * ncol, fit = kind == 0 ? 512 : 2048;
+    size_t best = 0;
+    for (int tc = 1; tc <= 8 && tc <= g.nt; tc++) {
+        const size_t cost = (tiles * ((g.nt + tc - 1) / tc) + fit - 1) / fit * (tc + 1);
+        if (best == 0 || cost < best) {
+            best = cost;
+            sc.tc = tc;
+        }
+    }
+    sc.remap = ncol % 8 == 0 && ncol > 8 ? 0 : 1;
     return sc;
 }
 
