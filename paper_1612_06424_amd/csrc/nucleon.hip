@@ -38,6 +38,7 @@
 #include <cstdlib>
 #include <cstring>
 
+#include "dd_gemm_plan.h"
 #include "dd_internal.h"
 #include "dd_wilson.h"
 
@@ -138,48 +139,10 @@ __global__ __launch_bounds__(kNB) void k_diquarks(int n, long long nsite, long l
 // adds them in a fixed order, so the result does not depend on scheduling.
 typedef double dbl4 __attribute__((ext_vector_type(4)));
 typedef double dbl2 __attribute__((ext_vector_type(2)));
-constexpr int kGM = 64, kGK = 16;  // rows of a workgroup's tile (complex entries) and k step
 constexpr int kGThreads = 256;
 
 __device__ __forceinline__ dbl2 gload2(rsrc_t r, uint32_t voff) {
     return __builtin_bit_cast(dbl2, __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, 0, 0));
-}
-
-// Blocks of 16 columns per wavefront (tile width 32 nj): the width that pads N least, one block only if it
-// saves more than a tenth (its LDS reads per MFMA are twice those of three: 100 vectors, 416 columns of it 3.92 ms,
-// 448 of two 3.88), and the wider of two that pad alike.  120 vectors: 480 columns of three, 512 of two.
-int zgemm_blocks(int N) {
-    const auto cost = [&](int nj) { return (N + 32 * nj - 1) / (32 * nj) * nj * (nj == 1 ? 1.1 : 1.0); };
-    int best = 1;
-    for (int nj = 2; nj <= 3; nj++)
-        if (cost(nj) <= cost(best)) best = nj;
-    return best;
-}
-
-// Splits of the k range for ntile tiles of nj blocks, nkt steps of k and MN entries: the least of the estimated
-// times of the product and of writing and adding the partial results, with at most about 16 workgroups per CU
-// in all.  A step of a wavefront is 32 nj MFMAs of 64 cycles; w workgroups on a CU share its matrix cores, and a
-// step has 1.1 us of latency that only the others hide; `fit` workgroups run per CU, the last round with as
-// many as are left, and a tenth of a round is lost to uneven ends.  Blocks on one 16^3
-// slice, 16 workgroups per CU throughout and so, ms: 4 vectors 0.23 and 0.075, 24 0.27 and 0.15, 48 0.61
-// and 0.54, 80 1.92 and 1.87.
-int zgemm_splits(int ntile, int nj, int nkt, size_t MN) {
-    const int fit = nj == 3 ? 2 : nj == 2 ? 3 : 5, lim = std::max(1, std::min(nkt, (16 * 256 + ntile - 1) / ntile));
-    const double mfma = 2048.0 * nj / 2.35e3;  // us of a step per workgroup on the CU
-    const auto step = [&](long long w) { return w ? std::max((double)w * mfma, mfma + 1.1) : 0.0; };
-    int best = 1;
-    double best_us = 1e30;
-    for (int ns = 1; ns <= lim; ns++) {
-        const int kps = (nkt + ns - 1) / ns;
-        const long long wgs = (long long)ntile * ns, full = wgs / (256 * fit), rem = wgs % (256 * fit);
-        const double us = kps * ((double)full * step(fit) + step((rem + 255) / 256) + 0.1 * step(fit)) +
-                          ns * (0.15 + (double)MN * 2 * sizeof(cpx<double>) / 5e6);
-        if (us < best_us) {
-            best_us = us;
-            best = ns;
-        }
-    }
-    return best;
 }
 
 template <int NJ>
@@ -495,10 +458,9 @@ dd_status baryon_blocks(dd_ctx* c, int n, int nt, const cpx<double>* s, cpx<doub
     cpx<double>* Sp = (cpx<double>*)workspace(c, W_DISC3, (size_t)3 * X * 4 * n * sizeof(cpx<double>), &e);
     if (e != DD_OK) return e;
     const int N = 4 * n;
-    const int nj = zgemm_blocks(N);
+    const GemmPlan plan = zgemm_plan(M, N, (3 * X + kGK - 1) / kGK);  // of a whole chunk; a last one has no more splits
+    const int nj = plan.nj, nsplit_max = plan.ns;
     const int ntile = (int)(((M + kGM - 1) / kGM) * ((N + 32 * nj - 1) / (32 * nj)));
-    const int nkt_max = (3 * X + kGK - 1) / kGK;
-    const int nsplit_max = zgemm_splits(ntile, nj, nkt_max, M * N);  // of a whole chunk; a last one has no more
     cpx<double>* Cpart =
         (cpx<double>*)workspace(c, W_DISC1, (size_t)nsplit_max * M * N * sizeof(cpx<double>), &e);
     if (e != DD_OK) return e;
