@@ -219,13 +219,14 @@ void launch_dslash(dd_ctx* c, const Geo& g, const cpx<R>* U, double kappa, int d
                    const cpx<R>* in, cpx<R>* out, const cpx<R>* aux, int ncol,
                    double* partial, const ColState* state);
 
-// Number of partial-sum slots per column written by one stencil launch.
-StencilSched stencil_sched(dd_ctx* c, const Geo& g, int kind, int ncol);
+// Shape of a stencil launch; sums: its epilogue forms sums.
+StencilSched stencil_sched(dd_ctx* c, const Geo& g, int kind, int ncol, bool sums);
+// Number of partial-sum slots per column written by one stencil launch that forms sums.
 int stencil_slots(dd_ctx* c, const Geo& g, int kind, int ncol);
 // Tuned shapes shared across processes through the file named by DD_TUNE_CACHE.
 void tune_cache_load(dd_ctx* c);
 void tune_cache_store(dd_ctx* c, const std::string& key, const StencilSched& sc);
-StencilSched default_sched(const Geo& g, int kind, int ncol);
+StencilSched default_sched(const Geo& g, int kind, int ncol, bool sums);
 int stencil_blocks(const Geo& g, const StencilSched& sc);
 int sched_kc(const StencilSched& sc, int ncol, size_t real_bytes, size_t col_bytes);
 int brick_rows(const Geo& g, int nt);
@@ -239,7 +240,7 @@ inline bool stencil_timed(const Geo& g, int ncol) { return (size_t)g.nsite * nco
 // workgroup: whether a field can take it (a brick fits, a column is below 2 GiB), whether a launch does
 // where no stored shape says otherwise, its partial slots per column (bricks).
 bool dslash_lds_ok(const Geo& g, size_t real_bytes);
-bool dslash_lds_form(const Geo& g, size_t real_bytes, int ncol);
+bool dslash_lds_form(const Geo& g, size_t real_bytes, int ncol, bool sums);
 int dslash_lds_blocks(const Geo& g);
 template <typename R>
 void launch_dslash_lds(dd_ctx* c, const Geo& g, const StencilSched& sc, const cpx<R>* U, R mass, int dag, int epi,

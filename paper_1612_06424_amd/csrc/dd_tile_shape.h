@@ -100,22 +100,28 @@ inline bool dslash_tile_ok(int L, int nt, size_t real_bytes) {
 // Whether a launch on a field takes the form: by sizes alone, not by a timing, since the form adds the hops of a
 // site in another order than the sweep and a result must not depend on how two launches happened to be
 // timed (the launch shapes within a form give the same bits).  `timed`: the shape is timed, the best of each form
-// compared below (us, sweep and form); else the untimed shapes (default_sched).
+// compared below (us, sweep and form); else the untimed shapes (default_sched).  `sums`: the launch forms sums
+// (inside solves).
 // Untimed: bricks that give every CU two workgroups and are nearly full.
 // FP64: bricks three quarters full win with one column too (32 x 24^3 113 and 104, 64 x 32^3 1.00; 12 columns of
 // 6 x 16^3, 192 bricks, 51.9 and 44.3; but 4 of 32 x 14^3 58 and 61); down to 0.6 with columns to share the links (8 x
 // 40^3, 2 columns 209 and 223, 6 columns 590 and 551); below that never (8 x 48^3, 12 columns 2068 and 2518).
+// The sums cost the form 24 registers that it has to spill, the sweep few: full bricks still win (ms a
+// solve of the full operator, 12 columns: 30 x 15^3, 0.82 full, 77.8 and 75.0; 8 x 21^3 52.7 and 49.5; 8 x 32^3 173
+// and 162), others do not (16 x 24^3, 0.75 full, 160 and 162, 4 columns 52.8 and 56.9; 16 x 17^3, 0.71, 55.9 and 61.2).
 // FP32 moves half the bytes past the same instructions, so one column never pays (64 x 32^3 1.18 of the
 // sweep's time); from two on full bricks do (8 x 32^3 46.7 and 42.3), others with several columns and bricks
-// enough (4 columns of 32 x 24^3 188 and 174, of 48 x 12^3, 768 bricks, 1.05) or with all twelve (16 x 18^3 0.89).
-inline bool dslash_tile_form(int L, int nt, int ncol, size_t real_bytes, bool timed) {
+// enough (4 columns of 32 x 24^3 188 and 174, of 48 x 12^3, 768 bricks, 1.05, of 16 x 19^3, 1120, a solve 14.9 and
+// 15.8 ms) or with all twelve (16 x 18^3 0.89); sums spill nothing there.
+inline bool dslash_tile_form(int L, int nt, int ncol, size_t real_bytes, bool timed, bool sums) {
     if (!dslash_tile_ok(L, nt, real_bytes)) return false;
     const int bricks = eo_tile_blocks(dslash_tile_shape(L, nt));
     const double fill = (double)nt * L * L * L / ((double)kDslSites * bricks);
     if (!timed) return bricks >= 512 && fill >= 0.9;
     if (bricks < 192) return false;
+    if (real_bytes == 8 && sums) return fill >= 0.8;
     if (real_bytes == 8) return fill >= 0.75 || (fill >= 0.6 && ncol >= 6);
-    return ncol >= 2 && (fill >= 0.87 || (ncol >= 4 && fill >= 0.75 && bricks >= 1024) || (ncol >= 12 && fill >= 0.8));
+    return ncol >= 2 && (fill >= 0.87 || (ncol >= 4 && fill >= 0.75 && bricks >= 1536) || (ncol >= 12 && fill >= 0.8));
 }
 
 }  // namespace dd

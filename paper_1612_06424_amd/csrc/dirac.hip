@@ -125,9 +125,9 @@ int brick_rows(const Geo& g, int nt) {
 // The LDS-tile form (dslash_tile_form) takes all columns in one group, us, sweep and form: 16 x 16^3 FP64 1 column 16.6
 // and 15.4, 3 columns 31.9 and 27.3, FP32 20.1 and 16.4; 7 x 32^3 FP32 32.1 and 28.1; but 30 x 19^3 FP64 (a
 // quarter empty) 47.4 and 50.8, 16 x 8^3 with 12 columns (64 bricks) 16.6 and 45.9.
-StencilSched default_sched(const Geo& g, int kind, int ncol) {
+StencilSched default_sched(const Geo& g, int kind, int ncol, bool sums) {
     StencilSched sc;
-    if (dslash_lds_form(g, kind == 0 ? 8 : 4, ncol)) {
+    if (dslash_lds_form(g, kind == 0 ? 8 : 4, ncol, sums)) {
         sc.nt = 256;
         sc.tc = 1;
         sc.remap = 1;
@@ -212,7 +212,8 @@ template <typename R>
 void launch_dslash(dd_ctx* c, const Geo& g, const cpx<R>* U, double kappa, int dag, int epi,
                    const cpx<R>* in, cpx<R>* out, const cpx<R>* aux, int ncol, double* partial,
                    const ColState* st) {
-    launch_dslash_sched<R>(c, g, stencil_sched(c, g, sizeof(R) == 8 ? 0 : 1, ncol), U, kappa, dag, epi, in, out,
+    const bool sums = epi != EPI_STORE && epi != EPI_HOP;
+    launch_dslash_sched<R>(c, g, stencil_sched(c, g, sizeof(R) == 8 ? 0 : 1, ncol, sums), U, kappa, dag, epi, in, out,
                            aux, ncol, partial, st);
 }
 

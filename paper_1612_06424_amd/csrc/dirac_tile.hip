@@ -19,8 +19,8 @@ __global__ __launch_bounds__(kDslNT, 2) void k_dslash_lds(Geo g, EoTile ts, Tile
 
 bool dslash_lds_ok(const Geo& g, size_t real_bytes) { return dslash_tile_ok(g.L, g.nt, real_bytes); }
 
-bool dslash_lds_form(const Geo& g, size_t real_bytes, int ncol) {
-    return dslash_tile_form(g.L, g.nt, ncol, real_bytes, stencil_timed(g, ncol));
+bool dslash_lds_form(const Geo& g, size_t real_bytes, int ncol, bool sums) {
+    return dslash_tile_form(g.L, g.nt, ncol, real_bytes, stencil_timed(g, ncol), sums);
 }
 
 int dslash_lds_blocks(const Geo& g) { return eo_tile_blocks(dslash_tile_shape(g.L, g.nt)); }

@@ -34,8 +34,8 @@ std::string key_of(const Geo& g, int kind, int ncol) {
 }
 
 template <typename R>
-StencilSched tune(dd_ctx* c, const Geo& g, int ncol) {
-    StencilSched best = default_sched(g, sizeof(R) == 8 ? 0 : 1, ncol);
+StencilSched tune(dd_ctx* c, const Geo& g, int ncol, bool sums) {
+    StencilSched best = default_sched(g, sizeof(R) == 8 ? 0 : 1, ncol, sums);
     const size_t nf = (size_t)ncol * 12 * g.nsite, nl = (size_t)36 * g.vlink;
     cpx<R>*in = nullptr, *out = nullptr, *U = nullptr;
     if (hipMalloc(&in, nf * sizeof(cpx<R>)) != hipSuccess || hipMalloc(&out, nf * sizeof(cpx<R>)) != hipSuccess ||
@@ -144,23 +144,26 @@ void tune_cache_store(dd_ctx* c, const std::string& key, const StencilSched& sc)
     f << key << " " << sc.nt << " " << sc.tc << " " << sc.remap << " " << sc.kc << " " << sc.blocked << "\n";
 }
 
-StencilSched stencil_sched(dd_ctx* c, const Geo& g, int kind, int ncol) {
-    const std::string k = key_of(g, kind, ncol);
+StencilSched stencil_sched(dd_ctx* c, const Geo& g, int kind, int ncol, bool sums) {
+    // a shape of their own for launches with sums only where they take the other form
+    const size_t rb = kind == 0 ? 8 : 4;
+    const bool own = sums && dslash_lds_form(g, rb, ncol, true) != dslash_lds_form(g, rb, ncol, false);
+    const std::string k = (own ? "s" : "") + key_of(g, kind, ncol);
     auto it = c->sched.find(k);
     if (it != c->sched.end()) {
         StencilSched hit = it->second;  // (a stored shape may name a form that does not fit the field)
-        if ((hit.blocked & 8) && !dslash_lds_ok(g, kind == 0 ? 8 : 4)) hit.blocked = 0;
+        if ((hit.blocked & 8) && !dslash_lds_ok(g, rb)) hit.blocked = 0;
         return hit;
     }
-    StencilSched sc = default_sched(g, kind, ncol);
+    StencilSched sc = default_sched(g, kind, ncol, sums);
     if (c->autotune && stencil_timed(g, ncol))
-        sc = kind == 0 ? tune<double>(c, g, ncol) : tune<float>(c, g, ncol);
+        sc = kind == 0 ? tune<double>(c, g, ncol, sums) : tune<float>(c, g, ncol, sums);
     tune_cache_store(c, k, sc);
     return sc;
 }
 
 int stencil_slots(dd_ctx* c, const Geo& g, int kind, int ncol) {
-    return stencil_blocks(g, stencil_sched(c, g, kind, ncol));
+    return stencil_blocks(g, stencil_sched(c, g, kind, ncol, true));
 }
 
 }  // namespace dd

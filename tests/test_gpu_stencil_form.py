@@ -16,6 +16,11 @@ from helpers import gaussian_field, lib, random_links, step
 pytestmark = pytest.mark.gpu
 
 C128, C64 = torch.complex128, torch.complex64
+SUMS = [  # T, L, ncol, D in solves by the LDS tile: FP64 fields of bricks four fifths full
+    (16, 24, 2, False),                  # 0.75 full (dd_apply_dirac takes the tile there)
+    (10, 15, 8, True),                   # 320 bricks, 0.82 full
+    (8, 19, 5, False),                   # 0.77 full
+]
 UNTIMED = [  # T, L, dom, ncol, dtype, LDS tile
     (16, 16, None, 1, C128, True),       # 512 full bricks
     (15, 16, None, 1, C128, False),      # 480; one slice
@@ -36,9 +41,9 @@ TIMED = [  # T, L, ncol, dtype, LDS tile
     (4, 36, 6, C128, False),             # 0.56 full
     (10, 30, 1, C64, False),
     (10, 30, 2, C64, True),              # 0.94 full
-    (8, 24, 4, C64, True),               # 1152 bricks, 0.75 full
-    (8, 24, 3, C64, False),
-    (7, 24, 4, C64, False),              # 1008 bricks
+    (11, 24, 4, C64, True),              # 1584 bricks, 0.75 full
+    (11, 24, 3, C64, False),
+    (10, 24, 4, C64, False),             # 1440 bricks
     (8, 18, 12, C64, True),              # 432 bricks, 0.84 full
     (8, 18, 11, C64, False),
 ]
@@ -94,3 +99,24 @@ def test_timed_form_and_bits(T, L, ncol, dtype, tile, monkeypatch, tmp_path):
         other, oname = _apply(dd, T, L, None, Ud, pd, 0.1287)
         assert oname.split("<")[0] == name.split("<")[0]
         assert torch.equal(other, out), (name, shape)
+
+
+@pytest.mark.parametrize("T,L,ncol,tile", SUMS)
+def test_form_inside_solves(T, L, ncol, tile, monkeypatch):
+    """Unpreconditioned FP64 solves: every launch (with sums) takes one form; dd_apply_dirac, without, its own."""
+    dd = lib()
+    step(f"form inside solves T={T} L={L} ncol={ncol}")
+    monkeypatch.delenv("DD_TUNE_CACHE", raising=False)
+    assert T * L ** 3 * ncol >= 2 ** 18
+    U = random_links(T, L, 0.3, 7300 + L)
+    b = gaussian_field(T * L ** 3, ncol, 7301)
+    ctx = dd.Context(T, L, -1)
+    dd.set_kernel_timing(ctx, True)
+    Ud, bd = dd.pack_links(U), dd.pack_field(b)
+    for solver in (0, 1):
+        x, st = dd.block_solve(ctx, Ud, 0.11, bd, None, dd.solver_params(tol=1e-10, solver=solver, precond=1))
+        assert max(st["true_rel_resid"][:ncol]) <= 1e-10
+        r = bd - dd.apply_dirac(ctx, Ud, 0.11, x)
+        assert (torch.linalg.norm(r) / torch.linalg.norm(bd)).item() <= 2e-10
+    names = [n for n in dd.kernel_timing(ctx) if not n.endswith("double, 0>") and ", 0, 0, " not in n]
+    assert names and all(n.startswith("k_dslash_lds<" if tile else "k_dslash<") for n in names), names

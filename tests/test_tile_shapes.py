@@ -22,8 +22,8 @@ void dslash_shape(int L, int nt, int* s) { dd::EoTile t = dd::dslash_tile_shape(
     int v[7] = {t.rt, t.ry, t.rz, t.ntt, t.nty, t.ntz, t.tb}; for (int k = 0; k < 7; k++) s[k] = v[k]; }
 int eo_ok(int L, int nt) { return dd::eo_tile_ok(L, nt); }
 int dslash_ok(int L, int nt, int bytes) { return dd::dslash_tile_ok(L, nt, (size_t)bytes); }
-int dslash_form(int L, int nt, int ncol, int bytes, int timed) {
-    return dd::dslash_tile_form(L, nt, ncol, (size_t)bytes, timed != 0); }
+int dslash_form(int L, int nt, int ncol, int bytes, int timed, int sums) {
+    return dd::dslash_tile_form(L, nt, ncol, (size_t)bytes, timed != 0, sums != 0); }
 int eo_form(int L, int nt, int ncol, int bytes) { return dd::eo_tile_form(L, nt, ncol, (size_t)bytes); }
 int eo_cols(int L, int nt, int ncol) { return dd::eo_tile_cols(L, nt, ncol); }
 void limits(int* s) { s[0] = dd::kTileSites; s[1] = dd::kDslSites; s[2] = dd::kDslHalo; }
@@ -91,9 +91,13 @@ def test_the_stencil_takes_the_form_only_where_it_fits(shapes):
             for nbytes in (4, 8):
                 for ncol in (1, 2, 4, 6, 12, 48):
                     timed = nt * L ** 3 * ncol >= 2 ** 18
-                    if shapes.dslash_form(L, nt, ncol, nbytes, int(timed)):
-                        assert shapes.dslash_ok(L, nt, nbytes), (L, nt, ncol, nbytes)
-                        taken += 1
+                    for sums in (0, 1):
+                        if shapes.dslash_form(L, nt, ncol, nbytes, int(timed), sums):
+                            assert shapes.dslash_ok(L, nt, nbytes), (L, nt, ncol, nbytes)
+                            taken += 1
+                    # launches with sums never take it where those without do not
+                    assert (shapes.dslash_form(L, nt, ncol, nbytes, int(timed), 1)
+                            <= shapes.dslash_form(L, nt, ncol, nbytes, int(timed), 0))
     assert taken > 0
 
 
