@@ -60,30 +60,17 @@ __device__ __forceinline__ void dslash_lds_body(const Geo& g, const EoTile& ts, 
 
     const int L = g.L, L2 = g.L2, L3 = g.L3, nt = g.nt, nsite = g.nsite;
     const uint32_t cs = (uint32_t)nsite * CB, fs = 12u * cs, ls = (uint32_t)g.vlink * CB;
-    const int ntile = ts.nty * ts.ntz;
-    const int tbk = blk_lin / (ts.tb * ntile);
-    const int inb = blk_lin - tbk * ts.tb * ntile;
-    const int tbs = min(ts.tb, ts.ntt - tbk * ts.tb);
-    int tile = inb / tbs;
-    const int bt = tbk * ts.tb + (inb - tile * tbs);
-    if (ts.nty % 4 == 0 && ts.ntz % 2 == 0) {
-        const int grp = tile >> 3, in8 = tile & 7, ng = ts.nty >> 2;
-        tile = ((grp / ng) * 2 + (in8 >> 2)) * ts.nty + (grp % ng) * 4 + (in8 & 3);
-    }
-    const int t0 = bt * ts.rt, y0 = (tile % ts.nty) * ts.ry, z0 = (tile / ts.nty) * ts.rz;
-    const int RT = min(ts.rt, nt - t0), RY = min(ts.ry, L - y0), RZ = min(ts.rz, L - z0);
-    const int blk = bt * ntile + tile;
+    const Brick bk = tile_brick(ts, blk_lin, L, nt);
+    const int blk = bk.blk;
 
     const int tid = (int)threadIdx.x;
     const bool partB = __builtin_amdgcn_readfirstlane(tid / NS) != 0;
     const int i = tid % NS;
-    const int nsit = RT * RZ * RY * L;
+    const int nsit = bk.RT * bk.RZ * bk.RY * L;
     const bool act = i < nsit;
     const int ic = min(i, nsit - 1);
-    const int row = ic / L, x = ic - row * L;
-    const int rr = row / RY, ry = row - rr * RY;
-    const int rt = rr / RZ, rz = rr - rt * RZ;
-    const int y = y0 + ry, z = z0 + rz, tl = t0 + rt;
+    const BrickSite bs = brick_site(bk, L, ic);
+    const int x = bs.x, y = bk.y0 + bs.ry, z = bk.z0 + bs.rz, tl = bk.t0 + bs.rt;
     const int sp = (z * L + y) * L + x;
     const int s = tl * L3 + sp;
     auto tglob = [&](int t) {
@@ -91,28 +78,6 @@ __device__ __forceinline__ void dslash_lds_body(const Geo& g, const EoTile& ts, 
         return tg >= g.T ? tg - g.T : tg;
     };
     const int sl = tglob(tl) * L3 + sp;  // this site's links
-    const int hy = RY < L ? 2 * RZ : 0, hz = RZ < L ? 2 * RY : 0, hrow = hy + hz;
-    const int nhalo = hrow * RT * L;
-    // field site of halo entry k (of site 0 of the brick where there is none)
-    auto halo_site = [&](int k) {
-        if (k >= nhalo) return t0 * L3 + (z0 * L + y0) * L;
-        int hr = k / L;
-        const int hx = k - hr * L;
-        const int ht = hr / hrow;
-        hr -= ht * hrow;
-        int yy, zz;
-        if (hr < hy) {
-            yy = hr < RZ ? y0 - 1 : y0 + RY;
-            zz = z0 + (hr < RZ ? hr : hr - RZ);
-        } else {
-            const int q = hr - hy;
-            zz = q < RY ? z0 - 1 : z0 + RZ;
-            yy = y0 + (q < RY ? q : q - RY);
-        }
-        yy = yy < 0 ? yy + L : (yy >= L ? yy - L : yy);
-        zz = zz < 0 ? zz + L : (zz >= L ? zz - L : zz);
-        return (t0 + ht) * L3 + (zz * L + yy) * L + hx;
-    };
     const size_t cst = (size_t)12 * (size_t)nsite;
     auto frsrc = [&](int c) { return make_rsrc(A.in + (size_t)c * cst, fs); };
     auto load = [&](rsrc_t f, uint32_t vo, cpx<R> (&p)[12]) {
@@ -233,7 +198,7 @@ __device__ __forceinline__ void dslash_lds_body(const Geo& g, const EoTile& ts, 
             w0[k] = phf != R(0) ? phf * w0[k] : mk<R>(0, 0);  // the link of a dropped hop may hold anything
             w1[k] = phb != R(0) ? phb * w1[k] : mk<R>(0, 0);
         }
-        const int ixp = row * L + (x == L - 1 ? 0 : x + 1), ixm = row * L + (x == 0 ? L - 1 : x - 1);
+        const BrickX nx = brick_x(bs, L);
         for (;;) {
             const int nxt = next_live(col + 1);
             cpx<R> pf[12], pb[12], a[12], hh[6];
@@ -259,10 +224,10 @@ __device__ __forceinline__ void dslash_lds_body(const Geo& g, const EoTile& ts, 
             if (it > 0) write_sum();
             if (PRE && nxt < col_hi) load(frsrc(nxt), v0, q);
             hop_fence<R>();
-            tile_project<R, ST, 1>(s_tile, loop_index<R>(ixp), hh, f);
+            tile_project<R, ST, 1>(s_tile, loop_index<R>(nx.xp), hh, f);
             hop_f<R, 1, false>(a, w2, hh, f);
             hop_fence<R>();
-            tile_project<R, ST, 1>(s_tile, loop_index<R>(ixm), hh, -f);
+            tile_project<R, ST, 1>(s_tile, loop_index<R>(nx.xm), hh, -f);
             hop_f<R, 1, true>(a, w3, hh, -f);
             hop_fence<R>();
             if (PRE) {
@@ -289,7 +254,11 @@ __device__ __forceinline__ void dslash_lds_body(const Geo& g, const EoTile& ts, 
         }
     } else {
         using PB = std::integral_constant<int, 1>;
-        const uint32_t v0 = (uint32_t)halo_site(i) * CB, v1 = (uint32_t)halo_site(NS + i) * CB;
+        auto halo_off = [&](int k) {
+            const HaloSite hs = halo_site(bk, L, L, k);
+            return (uint32_t)(hs.t * L3 + (hs.z * L + hs.y) * L + hs.x) * CB;
+        };
+        const uint32_t v0 = halo_off(i), v1 = halo_off(NS + i);
         cpx<R> q[12], q2[12];
         auto issue = [&](int c) {
             load(frsrc(c), v0, q);
@@ -300,11 +269,7 @@ __device__ __forceinline__ void dslash_lds_body(const Geo& g, const EoTile& ts, 
         link(2, sl + ((y == 0) ? (L - 1) * L : -L), w1);
         link(3, sl, w2);
         link(3, sl + ((z == 0) ? (L - 1) * L2 : -L2), w3);
-        const int h0 = NS + rt * hrow * L + x;
-        const int iym = ry > 0 ? ic - L : (RY < L ? h0 + rz * L : ic + (RY - 1) * L);
-        const int iyp = ry < RY - 1 ? ic + L : (RY < L ? h0 + (RZ + rz) * L : ic - (RY - 1) * L);
-        const int izm = rz > 0 ? ic - L * RY : (RZ < L ? h0 + (hy + ry) * L : ic + (RZ - 1) * RY * L);
-        const int izp = rz < RZ - 1 ? ic + L * RY : (RZ < L ? h0 + (hy + RY + ry) * L : ic - (RZ - 1) * RY * L);
+        const BrickYZ nb = brick_yz(bk, bs, L, L, NS, ic);
         for (;;) {
             const int nxt = next_live(col + 1);
             cpx<R> a[12], hh[6];
@@ -325,16 +290,16 @@ __device__ __forceinline__ void dslash_lds_body(const Geo& g, const EoTile& ts, 
             hop_fence<R>();
 #pragma unroll
             for (int k = 0; k < 12; k++) a[k] = mk<R>(0, 0);
-            tile_project<R, ST, 2>(s_tile, loop_index<R>(iyp), hh, f);
+            tile_project<R, ST, 2>(s_tile, loop_index<R>(nb.yp), hh, f);
             hop_f<R, 2, false>(a, w0, hh, f);
             hop_fence<R>();
-            tile_project<R, ST, 2>(s_tile, loop_index<R>(iym), hh, -f);
+            tile_project<R, ST, 2>(s_tile, loop_index<R>(nb.ym), hh, -f);
             hop_f<R, 2, true>(a, w1, hh, -f);
             hop_fence<R>();
-            tile_project<R, ST, 3>(s_tile, loop_index<R>(izp), hh, f);
+            tile_project<R, ST, 3>(s_tile, loop_index<R>(nb.zp), hh, f);
             hop_f<R, 3, false>(a, w2, hh, f);
             hop_fence<R>();
-            tile_project<R, ST, 3>(s_tile, loop_index<R>(izm), hh, -f);
+            tile_project<R, ST, 3>(s_tile, loop_index<R>(nb.zm), hh, -f);
             hop_f<R, 3, true>(a, w3, hh, -f);
             hop_fence<R>();
             cpx<R> pv[6], xv[6];

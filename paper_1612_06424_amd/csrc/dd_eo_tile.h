@@ -231,60 +231,27 @@ __device__ __forceinline__ void eo_tile_body(const Geo& g, const EoTile& ts, con
 
     const int L = g.L, L2 = g.L2, L3 = g.L3, LH = L >> 1, nt = g.nt, nh = g.nsite >> 1;
     const uint32_t cs = (uint32_t)nh * CB, fs = 12u * cs, ls = 2u * (uint32_t)nh * CB;
-    // workgroup -> brick: time fastest within a time block, then groups of 4 x 2 bricks in (y, z), whose
-    // halos lie mostly inside the group (both FP64 halves on 16 x 32^3: 951 us row by row, 922 so;
-    // FP32 the same either way)
-    const int ntile = ts.nty * ts.ntz;
-    const int tbk = blk_lin / (ts.tb * ntile);
-    const int inb = blk_lin - tbk * ts.tb * ntile;
-    const int tbs = min(ts.tb, ts.ntt - tbk * ts.tb);
-    int tile = inb / tbs;
-    const int bt = tbk * ts.tb + (inb - tile * tbs);
-    if (ts.nty % 4 == 0 && ts.ntz % 2 == 0) {
-        const int grp = tile >> 3, in8 = tile & 7, ng = ts.nty >> 2;
-        tile = ((grp / ng) * 2 + (in8 >> 2)) * ts.nty + (grp % ng) * 4 + (in8 & 3);
-    }
-    const int t0 = bt * ts.rt, y0 = (tile % ts.nty) * ts.ry, z0 = (tile / ts.nty) * ts.rz;
-    const int RT = min(ts.rt, nt - t0), RY = min(ts.ry, L - y0), RZ = min(ts.rz, L - z0);
-    const int blk = bt * ntile + tile;
+    const Brick bk = tile_brick(ts, blk_lin, L, nt);
+    const int blk = bk.blk;
 
     const int tid = (int)threadIdx.x;
     const bool partB = __builtin_amdgcn_readfirstlane(tid / NS) != 0;
     const int i = tid % NS;
-    const int nsit = RT * RZ * RY * LH;
+    const int nsit = bk.RT * bk.RZ * bk.RY * LH;
     const bool act = i < nsit;
     const int ic = min(i, nsit - 1);
-    const int row = ic / LH, xh = ic - row * LH;
-    const int rr = row / RY, ry = row - rr * RY;
-    const int rt = rr / RZ, rz = rr - rt * RZ;
-    const int y = y0 + ry, z = z0 + rz, tl = t0 + rt;
+    const BrickSite bs = brick_site(bk, LH, ic);
+    const int y = bk.y0 + bs.ry, z = bk.z0 + bs.rz, tl = bk.t0 + bs.rt;
     const int bo = (A.p_out + tl + y + z) & 1;
-    const int x = 2 * xh + bo;
+    const int x = 2 * bs.x + bo;
     const int sp = (z * L + y) * L + x;
     const int s = tl * L3 + sp, h = s >> 1;
-    // halo rows of a slice of the brick: y0 - 1 and y0 + RY (RZ rows each), z0 - 1 and z0 + RZ (RY rows each)
-    const int hy = RY < L ? 2 * RZ : 0, hz = RZ < L ? 2 * RY : 0, hrow = hy + hz;
     int sh0;  // the half site this thread stages
     if (!partB) {
-        sh0 = (tl * L3 + (z * L + y) * L) / 2 + xh;
+        sh0 = (tl * L3 + (z * L + y) * L) / 2 + bs.x;
     } else {
-        int hr = i / LH;
-        const int hx = i - hr * LH;
-        if (hr >= hrow * RT) hr = 0;  // nothing to stage: any site of the field
-        const int ht = hrow > 0 ? hr / hrow : 0;
-        hr -= ht * hrow;
-        int yy, zz;
-        if (hr < hy) {
-            yy = hr < RZ ? y0 - 1 : y0 + RY;
-            zz = z0 + (hr < RZ ? hr : hr - RZ);
-        } else {
-            const int k = hr - hy;
-            zz = k < RY ? z0 - 1 : z0 + RZ;
-            yy = y0 + (k < RY ? k : k - RY);
-        }
-        yy = yy < 0 ? yy + L : (yy >= L ? yy - L : yy);
-        zz = zz < 0 ? zz + L : (zz >= L ? zz - L : zz);
-        sh0 = ((t0 + ht) * L3 + (zz * L + yy) * L) / 2 + hx;
+        const HaloSite hs = halo_site(bk, L, LH, i);
+        sh0 = (hs.t * L3 + (hs.z * L + hs.y) * L) / 2 + hs.x;
     }
     constexpr bool PAIRED_LINKS = REC && sizeof(R) == 4;
     const uint32_t ubytes = PAIRED_LINKS ? 5u * (uint32_t)nh * 16u : 17u * (uint32_t)nh * CB;
@@ -403,8 +370,7 @@ __device__ __forceinline__ void eo_tile_body(const Geo& g, const EoTile& ts, con
             w0[k] = phf != R(0) ? phf * w0[k] : mk<R>(0, 0);  // the link of a dropped hop may hold anything
             w1[k] = phb != R(0) ? phb * w1[k] : mk<R>(0, 0);
         }
-        const int ixp = row * LH + (bo ? (xh + 1 == LH ? 0 : xh + 1) : xh);
-        const int ixm = row * LH + (bo ? xh : (xh == 0 ? LH - 1 : xh - 1));
+        const BrickX nx = brick_x_half(bs, LH, bo);
         for (;;) {
             const int nxt = next_col(col + 1);
             cpx<R> pf[12], pb[12], a[12], hh[6];
@@ -430,10 +396,10 @@ __device__ __forceinline__ void eo_tile_body(const Geo& g, const EoTile& ts, con
             if (it > 0) write_sum();
             if (sizeof(R) == 4 && nxt < col_hi) issue(nxt);
             hop_fence<R>();
-            tile_project<R, ST, 1>(s_tile, loop_index<R>(ixp), hh, f);
+            tile_project<R, ST, 1>(s_tile, loop_index<R>(nx.xp), hh, f);
             hop_f<R, 1, false>(a, w2, hh, f);
             hop_fence<R>();
-            tile_project<R, ST, 1>(s_tile, loop_index<R>(ixm), hh, -f);
+            tile_project<R, ST, 1>(s_tile, loop_index<R>(nx.xm), hh, -f);
             hop_f<R, 1, true>(a, w3, hh, -f);
             hop_fence<R>();
             if (sizeof(R) == 4) {
@@ -468,11 +434,7 @@ __device__ __forceinline__ void eo_tile_body(const Geo& g, const EoTile& ts, con
             if (col >= col_hi) return;
             issue(col);
         }
-        const int h0 = NS + rt * hrow * LH + xh;  // this slice's halo rows
-        const int iym = ry > 0 ? ic - LH : (RY < L ? h0 + rz * LH : ic + (RY - 1) * LH);
-        const int iyp = ry < RY - 1 ? ic + LH : (RY < L ? h0 + (RZ + rz) * LH : ic - (RY - 1) * LH);
-        const int izm = rz > 0 ? ic - LH * RY : (RZ < L ? h0 + (hy + ry) * LH : ic + (RZ - 1) * RY * LH);
-        const int izp = rz < RZ - 1 ? ic + LH * RY : (RZ < L ? h0 + (hy + RY + ry) * LH : ic - (RZ - 1) * RY * LH);
+        const BrickYZ nb = brick_yz(bk, bs, L, LH, NS, ic);
         for (;;) {
             const int nxt = next_col(col + 1);
             cpx<R> a[12], hh[6];
@@ -485,16 +447,16 @@ __device__ __forceinline__ void eo_tile_body(const Geo& g, const EoTile& ts, con
             hop_fence<R>();
 #pragma unroll
             for (int k = 0; k < 12; k++) a[k] = mk<R>(0, 0);
-            tile_project<R, ST, 2>(s_tile, loop_index<R>(iyp), hh, f);
+            tile_project<R, ST, 2>(s_tile, loop_index<R>(nb.yp), hh, f);
             hop_f<R, 2, false>(a, w0, hh, f);
             hop_fence<R>();
-            tile_project<R, ST, 2>(s_tile, loop_index<R>(iym), hh, -f);
+            tile_project<R, ST, 2>(s_tile, loop_index<R>(nb.ym), hh, -f);
             hop_f<R, 2, true>(a, w1, hh, -f);
             hop_fence<R>();
-            tile_project<R, ST, 3>(s_tile, loop_index<R>(izp), hh, f);
+            tile_project<R, ST, 3>(s_tile, loop_index<R>(nb.zp), hh, f);
             hop_f<R, 3, false>(a, w2, hh, f);
             hop_fence<R>();
-            tile_project<R, ST, 3>(s_tile, loop_index<R>(izm), hh, -f);
+            tile_project<R, ST, 3>(s_tile, loop_index<R>(nb.zm), hh, -f);
             hop_f<R, 3, true>(a, w3, hh, -f);
             hop_fence<R>();
             cpx<R> sv[6], xv[6];
