@@ -211,9 +211,13 @@ inline bool dslash_tile_ok(int L, int nt, size_t real_bytes) {
 // compared below (us, sweep and form); else the untimed shapes (default_sched).  `sums`: the launch forms sums
 // (inside solves).
 // Untimed: bricks that give every CU two workgroups and are nearly full.
-// FP64: bricks three quarters full win with one column too (32 x 24^3 113 and 104, 64 x 32^3 1.00; 12 columns of
-// 6 x 16^3, 192 bricks, 51.9 and 44.3; but 4 of 32 x 14^3 58 and 61); down to 0.6 with columns to share the links (8 x
-// 40^3, 2 columns 209 and 223, 6 columns 590 and 551); below that never (8 x 48^3, 12 columns 2068 and 2518).
+// Links past the 256 MB Infinity Cache are read from HBM, which the sweep does best where its x hops need no loads (L
+// divides 64) and its columns go by ones or twos: us FP64, 64 x 32^3 1 column 444 and 482, 2 669 and 754, 3 1121 and
+// 1012, 4 of 48 x 32^3 936 and 959, 6 1557 and 1339; 128 x 16^3 116 and 141, 175 and 222, 265 and 279, 305 and 363, 477
+// and 498; FP32 64 x 32^3 2 columns 407 and 428.  (12 x 32^3, links of 227 MB, 91 and 85, 138 and 135.)
+// FP64: bricks three quarters full win with one column too (32 x 24^3 113 and 104; 12 columns of 6 x 16^3, 192
+// bricks, 51.9 and 44.3; but 4 of 32 x 14^3 58 and 61); down to 0.6 with columns to share the links (8 x 40^3, 2 columns
+// 209 and 223, 6 columns 590 and 551); below that never (8 x 48^3, 12 columns 2068 and 2518).
 // The sums cost the form 24 registers that it has to spill, the sweep few: full bricks still win (ms a
 // solve of the full operator, 12 columns: 30 x 15^3, 0.82 full, 77.8 and 75.0; 8 x 21^3 52.7 and 49.5; 8 x 32^3 173
 // and 162), others do not (16 x 24^3, 0.75 full, 160 and 162, 4 columns 52.8 and 56.9; 16 x 17^3, 0.71, 55.9 and 61.2).
@@ -227,6 +231,8 @@ inline bool dslash_tile_form(int L, int nt, int ncol, size_t real_bytes, bool ti
     const double fill = (double)nt * L * L * L / ((double)kDslSites * bricks);
     if (!timed) return bricks >= 512 && fill >= 0.9;
     if (bricks < 192) return false;
+    const bool lanes = L >= 4 && 64 % L == 0;
+    if (lanes && (size_t)72 * real_bytes * nt * L * L * L > ((size_t)256 << 20) && (ncol <= 2 || ncol == 4)) return false;
     if (real_bytes == 8 && sums) return fill >= 0.8;
     if (real_bytes == 8) return fill >= 0.75 || (fill >= 0.6 && ncol >= 6);
     return ncol >= 2 && (fill >= 0.87 || (ncol >= 4 && fill >= 0.75 && bricks >= 1536) || (ncol >= 12 && fill >= 0.8));

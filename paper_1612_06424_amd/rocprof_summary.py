@@ -32,7 +32,8 @@ import sys
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 # the sources that decide what the stencil kernels do and how they are launched
-STENCIL_SOURCES = ["csrc/dd_dslash.h", "csrc/dd_dslash_tile.h", "csrc/dd_eo.h", "csrc/dd_eo_tile.h", "csrc/dd_wilson.h",
+STENCIL_SOURCES = ["csrc/dd_dslash.h", "csrc/dd_dslash_tile.h", "csrc/dd_eo.h", "csrc/dd_eo_tile.h", "csrc/dd_tile_shape.h",
+                   "csrc/dd_wilson.h",
                    "csrc/dd_internal.h", "csrc/dirac.hip", "csrc/dirac_tile.hip", "csrc/evenodd.hip", "csrc/batched.hip",
                    "csrc/tune.hip", "tune_cache_mi355x.txt"]
 

@@ -39,6 +39,8 @@ TIMED = [  # T, L, ncol, dtype, LDS tile
     (16, 22, 2, C128, False),            # 0.69 full
     (16, 22, 6, C128, True),
     (4, 36, 6, C128, False),             # 0.56 full
+    (16, 32, 2, C128, False),            # links past 256 MB, L divides 64
+    (13, 32, 2, C128, True),             # 245 MB
     (10, 30, 1, C64, False),
     (10, 30, 2, C64, True),              # 0.94 full
     (11, 24, 4, C64, True),              # 1584 bricks, 0.75 full
