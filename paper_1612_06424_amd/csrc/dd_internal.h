@@ -157,6 +157,7 @@ struct dd_ctx {
     // autotuned stencil launch shapes, keyed by (precision, ncol, geometry)
     std::map<std::string, dd::StencilSched> sched;
     int autotune = 1;
+    int full_solve = 0;  // inside a solve of the full operator: launches with sums have timed shapes of their own
     // library-owned stream for work captured into HIP graphs (created on first use)
     hipStream_t own_stream = nullptr;
     // pinned host mirrors of per-column state and of small reductions

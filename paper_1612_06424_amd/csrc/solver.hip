@@ -698,6 +698,11 @@ dd_status solve(dd_ctx* c, const cpx<double>* U, double kappa, const Geo& g, int
                 cpx<double>* x, const dd_solver_params& p, dd_solve_stats* stats, int dag) {
     if (p.precond == DD_PRECOND_EO && eo_applicable(g)) return solve_eo(c, U, kappa, g, ncol, b, x, p, stats, dag);
     const auto t_start = std::chrono::steady_clock::now();
+    struct FullSolve {  // until the solve returns
+        dd_ctx* c;
+        explicit FullSolve(dd_ctx* ctx) : c(ctx) { c->full_solve = 1; }
+        ~FullSolve() { c->full_solve = 0; }
+    } full_solve(c);
     SingleSystem S;
     S.c = c;
     S.g = g;

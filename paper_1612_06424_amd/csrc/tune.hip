@@ -15,6 +15,7 @@
 // loads the choices stored there and every new choice is appended to it, so
 // that separate processes (for instance the passes of a profiler) launch the
 // same shapes.
+#include <algorithm>
 #include <chrono>
 #include <cstdio>
 #include <cstdlib>
@@ -34,12 +35,16 @@ std::string key_of(const Geo& g, int kind, int ncol) {
 }
 
 template <typename R>
-StencilSched tune(dd_ctx* c, const Geo& g, int ncol, bool sums) {
+StencilSched tune(dd_ctx* c, const Geo& g, int ncol, bool sums) {  // sums: timed with |D in|^2
     StencilSched best = default_sched(g, sizeof(R) == 8 ? 0 : 1, ncol, sums);
     const size_t nf = (size_t)ncol * 12 * g.nsite, nl = (size_t)36 * g.vlink;
+    // slots of the shapes below: tiles of 128 sites and chunks of one slice, or bricks
+    const size_t slots = std::max((size_t)((g.L3 + 127) / 128) * g.nt, (size_t)dslash_lds_blocks(g)) * ncol;
     cpx<R>*in = nullptr, *out = nullptr, *U = nullptr;
+    double* partial = nullptr;
     if (hipMalloc(&in, nf * sizeof(cpx<R>)) != hipSuccess || hipMalloc(&out, nf * sizeof(cpx<R>)) != hipSuccess ||
-        hipMalloc(&U, nl * sizeof(cpx<R>)) != hipSuccess) {
+        hipMalloc(&U, nl * sizeof(cpx<R>)) != hipSuccess ||
+        (sums && hipMalloc((void**)&partial, slots * 3 * sizeof(double)) != hipSuccess)) {
         (void)hipGetLastError();
         if (in) (void)hipFree(in);
         if (out) (void)hipFree(out);
@@ -58,7 +63,8 @@ StencilSched tune(dd_ctx* c, const Geo& g, int ncol, bool sums) {
         auto time = [&](int n) {
             (void)hipEventRecord(e0, c->stream);
             for (int r = 0; r < n; r++)
-                launch_dslash_sched<R>(c, g, sc, U, 0.125, 0, EPI_STORE, in, out, nullptr, ncol, nullptr, nullptr);
+                launch_dslash_sched<R>(c, g, sc, U, 0.125, 0, sums ? EPI_NORM : EPI_STORE, in, out, nullptr, ncol,
+                                        partial, nullptr);
             (void)hipEventRecord(e1, c->stream);
             (void)hipEventSynchronize(e1);
             float t = 0;
@@ -113,6 +119,7 @@ StencilSched tune(dd_ctx* c, const Geo& g, int ncol, bool sums) {
     (void)hipFree(in);
     (void)hipFree(out);
     (void)hipFree(U);
+    if (partial) (void)hipFree(partial);
     (void)hipGetLastError();
     return best;
 }
@@ -145,9 +152,12 @@ void tune_cache_store(dd_ctx* c, const std::string& key, const StencilSched& sc)
 }
 
 StencilSched stencil_sched(dd_ctx* c, const Geo& g, int kind, int ncol, bool sums) {
-    // a shape of their own for launches with sums only where they take the other form
+    // launches with sums have a shape of their own where they take the other form, and in solves of the full operator,
+    // which launch hardly anything else: the FP32 sweep with sums pays for two columns per thread what the one
+    // without does not (16 x 17^3, 4 columns: 51 us a launch in D's shape, 39 in its own)
     const size_t rb = kind == 0 ? 8 : 4;
-    const bool own = sums && dslash_lds_form(g, rb, ncol, true) != dslash_lds_form(g, rb, ncol, false);
+    const bool own = sums && stencil_timed(g, ncol) &&
+                     (c->full_solve || dslash_lds_form(g, rb, ncol, true) != dslash_lds_form(g, rb, ncol, false));
     const std::string k = (own ? "s" : "") + key_of(g, kind, ncol);
     auto it = c->sched.find(k);
     if (it != c->sched.end()) {
