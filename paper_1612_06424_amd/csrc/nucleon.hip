@@ -133,9 +133,9 @@ __global__ __launch_bounds__(kNB) void k_diquarks(int n, long long nsite, long l
 // the current one is multiplied), and each wavefront runs 8 NJ MFMAs per 4 values of
 // k on its 32 x 16 NJ quarter (NJ = 3: 184 registers, two wavefronts per SIMD; NJ = 2: 132
 // registers, three; a form of that holding the step's operands up front took 212 and ran 16 %
-// slower).  What bounds it: the matrix cores, busy 97 % of the time at the clock that the card holds;
-// tiles 64 wide spent 6 % of it on padding 480 columns (120 vectors) to 512: per 6162 sites 7.25
-// ms, 96 wide 6.93.  Each split writes its own partial C; k_zgemm_reduce
+// slower).  What bounds it: the matrix cores, busy 83 % of their cycles (the CUs 97 %) at the 2.37 GHz that the
+// card holds; a chunk of 6162 sites of 120 vectors, 480 columns: 8.03 ms, 64.2 TFLOP/s, 96 wide; 64 wide, padded to 512
+// columns, a slice of 32^3 takes 4 % longer (48.6 ms and 47.0).  Each split writes its own partial C; k_zgemm_reduce
 // adds them in a fixed order, so the result does not depend on scheduling.
 typedef double dbl4 __attribute__((ext_vector_type(4)));
 typedef double dbl2 __attribute__((ext_vector_type(2)));
