@@ -173,8 +173,8 @@ inline int eo_tile_cols(int L, int nt, int ncol) {
 // 8 x 18^3 (96 bricks, three columns one after the other) 4.61 and 4.27, 6 of 20 x 10^3 3.41 and 3.13.
 // FP64: where a whole workgroup per CU has columns to loop over and the bricks are full (us a half hop, 12 columns:
 // 16 x 32^3, 1024 bricks, 418 against the sweep's 579; 32 x 16^3, 256 bricks, 86 against 140; 8 x 16^3, 64 bricks, 36
-// against 31; solves, ms: 4 columns of 16 x 20^3 14.3 and 16.6, 12 of 4 x 40^3, 0.64 full, 85 and 74, 4 of 2 x 96^3, 0.38 full,
-// 302 and 142).
+// against 31; solves, ms: 4 columns of 16 x 20^3 14.3 and 16.6, 12 of 4 x 40^3, 0.64 full, 85 and 74, 4 of 2 x 96^3,
+// 0.19 full, 302 and 142).
 inline bool eo_tile_form(int L, int nt, int ncol, size_t real_bytes) {
     const int bricks = eo_tile_blocks(eo_tile_shape(L, nt));
     if (bricks == 0) return false;

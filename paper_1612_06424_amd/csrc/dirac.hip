@@ -116,10 +116,10 @@ int brick_rows(const Geo& g, int nt) {
 // Shape of a launch too small to be timed, or of one whose timing found no memory (kind 0: FP64, 1: FP32).  Of
 // the sweep: a chunk of tc slices is a serial chain of tc + 1 steps of 2 to 6 us (its first slice loads its
 // backward neighbours too), and the workgroups run in rounds of 512 in FP64 (one wavefront a SIMD), 2048 in
-// FP32, so the chunk is taken that makes rounds times steps least.  us, chunks of 8 slices in hardware order, of 1 to 4 by the mean
-// wavefronts per SIMD, and so: 16 x 4^3 FP64 1 column 29.9, 6.2, 6.2; 11 x 15^3 FP32 5 columns 42.6, 22.3, 22.3; 16 x 8^3
-// FP64 12 columns 39.9, 17.6, 17.6; 9 x 13^3 FP64 12 columns 53.5, 67.9 (two rounds of 4 slices, the second nearly
-// empty), 46.3; 6 x 11^3 FP64 24 columns 35.6, 60.5, 37.9.
+// FP32, so the chunk is taken that makes rounds times steps least.  us, chunks of 8 slices in hardware order, of 1 to
+// 4 by the mean wavefronts per SIMD, and so: 16 x 4^3 FP64 1 column 29.9, 6.2, 6.2; 11 x 15^3 FP32 5 columns 42.6,
+// 22.3, 22.3; 16 x 8^3 FP64 12 columns 39.9, 17.6, 17.6; 9 x 13^3 FP64 12 columns 53.5, 67.9 (two rounds of 4 slices,
+// the second nearly empty), 46.3; 6 x 11^3 FP64 24 columns 35.6, 60.5, 37.9.
 // Workgroups in XCD-contiguous ranges (22.3 us against 34 for the 11 x 15^3 case), but in hardware order where the
 // columns are a larger multiple of 8: each XCD then keeps to the same columns (24 columns of 6 x 11^3 38.7 and 42.5).
 // The LDS-tile form (dslash_tile_form) takes all columns in one group, us, sweep and form: 16 x 16^3 FP64 1 column 16.6
